@@ -143,25 +143,10 @@ __device__ __forceinline__ int64_t* budget_of(int32_t* cnt) {
   return reinterpret_cast<int64_t*>(cnt + kCntBudget);
 }
 
-// Exclusive count of `pred` over a 256-thread block in thread order: wavefront
-// ballot + popcount of the lanes below (mbcnt), plus the per-wave totals.
-// Also returns the block total.  Every thread of the block must call it.
-__device__ __forceinline__ int block_exclusive_count(bool pred, int* s_wave, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const unsigned long long mask = __ballot(pred);
-  const int below = __popcll(mask & ((1ull << lane) - 1ull));
-  if (lane == 0) s_wave[wave] = __popcll(mask);
-  __syncthreads();
-  int base = 0;
-  total = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const int cw = s_wave[w];
-    base += (w < wave) ? cw : 0;
-    total += cw;
-  }
-  __syncthreads();
-  return base + below;
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+// Lanes below this one in a ballot.
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 __device__ __forceinline__ void load_table(const TableColumn& tab, uint8_t* s_a0, uint8_t* s_amin) {
@@ -180,58 +165,179 @@ __device__ __forceinline__ int clamp_n_new(const AppendArgs& a, int b, uint32_t&
   return n;
 }
 
-// Exclusive counts of N predicates over a block of kWaves waves in thread
-// order (a wavefront ballot and the popcount of the lanes below for each, plus
-// the per-wave totals in s_wave), and the block totals: two barriers for all
-// N.  Every thread of the block must call it.
-template <int N, int kWaves>
-__device__ __forceinline__ void block_counts(const bool (&pred)[N], int (*s_wave)[kWaves], int (&excl)[N],
-                                             int (&total)[N]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int below[N];
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const unsigned long long mask = __ballot(pred[k]);
-    below[k] = __popcll(mask & ((1ull << lane) - 1ull));
-    if (lane == 0) s_wave[k][wave] = __popcll(mask);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    int base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const int cw = s_wave[k][w];
-      base += (w < wave) ? cw : 0;
-      tot += cw;
-    }
-    excl[k] = base + below[k];
-    total[k] = tot;
-  }
-  __syncthreads();
+__device__ __forceinline__ int ring_page(const CacheView& cv, int b, int layer, int k) {
+  return (b * cv.n_layers + layer) * cv.ring_pp + k;
+}
+__device__ __forceinline__ uint8_t* ring_act_of(const CacheView& cv, int b, int layer) {
+  return cv.ring_act + ((size_t)b * cv.n_layers + layer) * cv.window;
 }
 
-// One block of kPlanThreads threads per sequence walks the call's tokens in
-// chunks of kPlanThreads.  kBudget: the tokens carry parser states and the
-// online controller decides (one thread walks each chunk's tokens in position
-// order, the table in LDS).
+// The controller's decisions of the tokens that the budget does not constrain
+// or constrains wholly, per tag (Alg. 2): with at least `cost_u` bytes left
+// nothing is demoted and, in a critical state (index 1), every group climbs
+// while its next upgrade scores above 0 (whatever the order, all of them
+// fit); with none left, or fewer than `cost_f`, every group sits at its floor
+// and nothing fits to be promoted.  Costs are below 2^20 (128 layers of 4 KiB).
+struct BudgetFast {
+  int cost_u[2][PASK_MAX_TAGS], cost_f[PASK_MAX_TAGS];
+  uint8_t act_u[2][PASK_MAX_TAGS], act_f[PASK_MAX_TAGS];   // action of the layer's group
+  int cost_high;                                           // a forced token: HIGH everywhere
+};
+__device__ __forceinline__ void budget_fast_table(const BudgetTable& t, int group, BudgetFast& f) {
+  const int z = (int)threadIdx.x, C = (int)t.n_groups;
+  if (z < PASK_MAX_TAGS) {
+    int cu0 = 0, cu1 = 0, cf = 0;
+    for (int c = 0; c < C; ++c) {
+      const int fl = t.floor_[z][c], a0 = max((int)t.action[z][c], fl);
+      int up = a0;
+      while (up < kHigh && t.rho_up[z][c][up] > 0.0f) ++up;
+      cu0 += (int)t.m[c][a0];
+      cu1 += (int)t.m[c][up];
+      cf += (int)t.m[c][fl];
+      if (c == group) {
+        f.act_u[0][z] = (uint8_t)a0;
+        f.act_u[1][z] = (uint8_t)up;
+        f.act_f[z] = (uint8_t)fl;
+      }
+    }
+    f.cost_u[0][z] = cu0;
+    f.cost_u[1][z] = cu1;
+    f.cost_f[z] = cf;
+  }
+  if (z == 0) {
+    int h = 0;
+    for (int c = 0; c < C; ++c) h += (int)t.m[c][kHigh];
+    f.cost_high = h;
+  }
+}
+
+// The controller over the tokens jj0..jj1-1 of a call, in position order, by
+// one wave: 64 tokens at a time, every lane guesses from the budget at hand
+// that its token is unconstrained (U) or at its floors (F), a prefix sum of
+// the guessed costs gives each token's exact budget as far as the guesses
+// before it hold, and the run up to the first token whose guess fails, or that
+// is neither U nor F, is taken at once; budget_decide takes that token.  F
+// holds for good once it holds (the budget never grows), so a run ends only
+// where a state's reserve is reached.  actions[jj - jj0] gets the layer's
+// action.  The plan kernel of 384 replayed tokens of 16 sequences (two groups)
+// took 420 us with one thread taking one token after another, 30 us so.
+__device__ __forceinline__ void budget_walk(const BudgetTable& t, const BudgetFast& f, const uint8_t* tags,
+                                            const uint8_t* states, int jj0, int jj1, int pos0, int group,
+                                            int64_t& R, uint32_t& flags, uint8_t* actions) {
+  const int lane = threadIdx.x & 63;
+  for (int base = jj0; base < jj1; base += 64) {
+    const int jj = base + lane;
+    const bool valid = jj < jj1;
+    const int tag = valid ? (int)tags[jj] : 0, state = valid ? (int)states[jj] : 0;
+    const bool forced = (uint32_t)(pos0 + jj) < t.n_sink || (uint32_t)tag >= t.n_tags;
+    const bool known = (uint32_t)state < t.n_states;
+    if (valid && !forced && !known) flags |= PASK_FLAG_BAD_STATE;
+    const int64_t gamma = known && !forced ? t.gamma[state] : 0;
+    const int crit = known && t.crit[state] != 0 ? 1 : 0;
+    const int z = forced ? 0 : tag;
+    const int cu = forced ? f.cost_high : f.cost_u[crit][z], cf = f.cost_f[z];
+    int act = 0;
+    for (int i0 = 0; i0 < 64 && base + i0 < jj1;) {   // lanes below i0 are decided
+      const int64_t left = R - gamma;
+      const bool u = forced || left >= cu, at_floor = !u && (left <= 0 || left < cf);
+      const bool open = valid && lane >= i0;
+      const int cost = open ? (u ? cu : (at_floor ? cf : 0)) : 0;
+      int incl = cost;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
+      }
+      const bool holds = u ? forced || left - (incl - cost) >= cu : at_floor;
+      const unsigned long long bad = __ballot(open && !holds);
+      const int k = bad ? __ffsll((long long)bad) - 1 : 64;   // first lane not taken
+      if (open && lane < k) act = forced ? kHigh : (u ? f.act_u[crit][z] : f.act_f[z]);
+      R -= k > 0 ? __shfl(incl, k - 1) : 0;
+      i0 = k;
+      if (k == 64) break;
+      // With its exact budget lane k's token may be U or F after all; else it
+      // is decided on its own.
+      const int64_t lk = R - gamma;
+      const bool own = lk > 0 && lk >= cf && lk < cu;
+      if ((__ballot(own) >> k) & 1ull) {
+        int64_t Rk = R;
+        if (lane == k) act = budget_decide(&t, tag, state, false, group, Rk, flags);
+        R = ((int64_t)__shfl((int)(Rk >> 32), k) << 32) | (uint32_t)__shfl((int)(uint32_t)Rk, k);
+        i0 = k + 1;
+      }
+    }
+    if (valid) actions[jj - jj0] = (uint8_t)act;
+  }
+}
+
+// The plan of a bulk append: one block of kPlanThreads threads per sequence
+// slots the call's tokens in chunks of kPlanChunk.  The combined index x
+// covers positions q = e0 + x, e0 = max(0, p0 - W): first the recent window's
+// tokens from before the call (x < nr = p0 - e0; their decisions in ring_act),
+// then the new tokens (j = x - nr).  Positions below p0 + n_fit - W leave the
+// window now (W = 0: every new token) and are slotted into the stores in
+// position order; the new tokens after them enter the window and their
+// decisions go to ring_act (after every read of ring_act in the chunk: the W
+// positions of the window after the call have distinct slots, so no slot
+// still in the window is overwritten).  The sequence's last four staging words
+// keep the stores' counts before the call, p0 and n_fit for the pack and
+// window-fill kernels.
+//
+// A wave takes `rounds` x 64 consecutive tokens of a chunk, a token per lane
+// and round, so that the tags of all rounds load at once, a token's rank is a
+// ballot's bits below its lane, and a chunk of up to 16,384 tokens costs one
+// exchange of the waves' totals and one page grant per store (slots are
+// consecutive, so the pages a chunk opens follow from its first and last
+// slot).  One block per sequence runs on one compute unit and is bound by its
+// vector instructions: a 256-entry table in LDS gives a tag's action, forced
+// and bad bits at once, and drops, losses and flags follow from the totals.
+// Against chunks of one token per thread, each with four exchanges (kernel
+// times): one 32,000-token labelled prompt 127.7 -> 21.9 us, 32 labelled
+// prompts of up to 16,384 tokens 68.3 -> 13.4 us, 64 kept prompts of up to
+// 8,192 tokens 31.1 -> 9.0 us.
+//
+// kBudget: the tokens carry parser states and wave 0 walks the controller over
+// the chunk first (table in LDS).
 constexpr int kPlanThreads = 1024, kPlanWaves = kPlanThreads / 64;
-template <bool kBudget>
+constexpr int kPlanRounds = 16, kPlanChunk = kPlanThreads * kPlanRounds;
+constexpr int kEntForced = 4, kEntBad = 8;         // beside the action's two bits
+template <bool kBudget, bool kWindow>
 __global__ __launch_bounds__(kPlanThreads) void append_plan_kernel(AppendArgs a) {
-  __shared__ uint8_t s_a0[64], s_amin[64];
-  __shared__ int s_wave[4][kPlanWaves];
+  __shared__ uint8_t s_tab[256];                   // per tag: action | kEntForced | kEntBad
+  __shared__ int2 s_wave[kPlanWaves];
   __shared__ unsigned s_page_base[2];
   __shared__ int s_granted[2];
+  __shared__ int s_forced;
   struct Empty {};
   __shared__ std::conditional_t<kBudget, BudgetTable, Empty> s_bud;
-  __shared__ uint8_t s_act[kBudget ? kPlanThreads : 1];
+  __shared__ std::conditional_t<kBudget, BudgetFast, Empty> s_fast;
+  __shared__ uint8_t s_act[kBudget ? kPlanChunk : 1];
   const CacheView& cv = a.cv;
   const int b = blockIdx.x;
-  load_table(a.tab, s_a0, s_amin);
+  const int W = kWindow ? cv.window : 0;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool keep_all = (a.flags & kKeepAll) != 0u;
+  if (threadIdx.x < 256) {
+    const uint32_t z = threadIdx.x;
+    const int forced = kHigh | kEntForced;
+    int e = keep_all ? forced : forced | kEntBad;
+    if (!keep_all && z < a.tab.n_tags) {
+      const int act = max((int)a.tab.a0[z], (int)a.tab.amin[z]);
+      e = act == kDrop || act == kHigh ? act : 1;
+    }
+    s_tab[z] = (uint8_t)e;
+  }
+  if (threadIdx.x == 0) s_forced = 0;
   uint32_t flags = 0;
   const int n = clamp_n_new(a, b, flags);
   int32_t* cnt = counters_of(cv, b, a.layer);
-  const int pos0 = cnt[kCntPos];
+  const int p0 = cnt[kCntPos];
+  const int n_fit = max(0, min(n, cv.max_tokens - p0));
+  if (n_fit < n) flags |= PASK_FLAG_SEQ_CAPACITY;
+  const int e0 = max(0, p0 - W), nr = p0 - e0;
+  const int n_out = max(e0, p0 + n_fit - W) - e0;    // entries leaving the window now
+  const int n_x = nr + n_fit;
+  const int n_sunk = (int)min(a.tab.n_sink, 0x7FFFFFFFu) - e0;   // x below it: a sink
   bool budget = false;
   int64_t R = 0;
   if constexpr (kBudget) {
@@ -241,111 +347,150 @@ __global__ __launch_bounds__(kPlanThreads) void append_plan_kernel(AppendArgs a)
     __syncthreads();
     budget = s_bud.loaded == kBudgetLoaded;
     if (!budget && threadIdx.x == 0) flags |= PASK_FLAG_NO_BUDGET;
-    if (budget && threadIdx.x == 0) R = *budget_of(cnt);
+    if (budget) {
+      R = *budget_of(cnt);
+      budget_fast_table(s_bud, (int)a.tab.group, s_fast);
+    }
   }
   int nst[2] = {cnt[kCntHi], cnt[kCntLo]};
-  int n_drop = 0, n_forced = 0, n_lost = 0, n_fit = 0;
-  int32_t* bt[2] = {block_table_of(cv, b, a.layer, kHi), block_table_of(cv, b, a.layer, kLo)};
-  int32_t* il[2] = {index_list_of(cv, b, a.layer, kHi), index_list_of(cv, b, a.layer, kLo)};
+  const int lost0 = cnt[kCntLost], drop0 = cnt[kCntDrop], forced0 = cnt[kCntForced];
+  int n_kept = 0, n_lost = 0, c_forced = 0;
+  int32_t* il = index_list_of(cv, b, a.layer, kHi);  // HIGH's list, then LOW's
+  int32_t* bt = block_table_of(cv, b, a.layer, kHi);
+  uint8_t* ract = kWindow ? ring_act_of(cv, b, a.layer) : nullptr;
   int32_t* stg = cv.staging + (size_t)b * cv.staging_stride;
-  if (threadIdx.x == 0) {                          // for the pack kernel: stores and position before the call
+  if (threadIdx.x == 0) {
     stg[cv.staging_stride - 4] = nst[0];
     stg[cv.staging_stride - 3] = nst[1];
-    stg[cv.staging_stride - 2] = pos0;
+    stg[cv.staging_stride - 2] = p0;
+    stg[cv.staging_stride - 1] = n_fit;
   }
-  const bool keep_all = (a.flags & kKeepAll) != 0u;
+  const uint8_t* tags = keep_all ? nullptr : a.tags + (size_t)b * a.max_new;
   const unsigned pool[2] = {(unsigned)cv.hi_pages, (unsigned)cv.lo_pages};
   __syncthreads();
 
-  // Every chunk's reads of the shared words (s_page_base, s_granted, s_act)
-  // come before the first barrier of the next chunk's counts, which every
-  // writer of the next chunk passes first: no barrier at the end of a chunk.
-  for (int c0 = 0; c0 < n; c0 += kPlanThreads) {
-    const int j = c0 + (int)threadIdx.x;
-    const bool valid = j < n;
-    const int pos = pos0 + j;
-    const bool fits = valid && pos < cv.max_tokens;
+  // Between two chunks: the words a chunk shares (s_wave, s_page_base,
+  // s_granted, s_act) are read before the first barrier of the next chunk that
+  // their writer there has passed, or between the chunk's own two barriers.
+  for (int c0 = 0; c0 < n_x; c0 += kPlanChunk) {
+    const int cm = min(kPlanChunk, n_x - c0);
+    const int rounds = (cm + kPlanThreads - 1) / kPlanThreads;
+    const int x0 = c0 + wave * 64 * rounds + lane;
     if constexpr (kBudget) {
-      if (budget && threadIdx.x == 0) {
-        const int j1 = min(min(n, c0 + kPlanThreads), cv.max_tokens - pos0);
-        const int group = (int)a.tab.group;
-        for (int jj = c0; jj < j1; ++jj) {
-          const size_t at = (size_t)b * a.max_new + jj;
-          const int tag = (int)a.tags[at];
-          const bool forced = (uint32_t)(pos0 + jj) < s_bud.n_sink || (uint32_t)tag >= s_bud.n_tags;
-          s_act[jj - c0] = (uint8_t)budget_decide(&s_bud, tag, (int)a.states[at], forced, group, R, flags);
-        }
-      }
+      const int jj0 = max(0, c0 - nr), jj1 = min(n_fit, c0 + kPlanChunk - nr);
+      if (budget && wave == 0)
+        budget_walk(s_bud, s_fast, tags, a.states + (size_t)b * a.max_new, jj0, jj1, p0, (int)a.tab.group, R, flags,
+                    s_act + (jj0 + nr - c0));
       __syncthreads();
     }
-    int act = kDrop;
-    bool forced = false, bad = false;
-    if (fits) {
-      const int tag = a.tags ? (int)a.tags[(size_t)b * a.max_new + j] : 0;
-      act = decide(s_a0, s_amin, a.tab.n_tags, a.tab.n_sink, keep_all, tag, pos, forced, bad);
-      if constexpr (kBudget) {
-        if (budget) act = s_act[threadIdx.x];
-      }
-    }
-    if (bad) flags |= PASK_FLAG_BAD_TAG;
-    if (valid && !fits) flags |= PASK_FLAG_SEQ_CAPACITY;
-    const int st = act == kHigh ? kHi : kLo;
-    const bool keep = fits && act != kDrop;
-    int rank[2], tot[2], prank[2], np[2];
-    block_counts<2, kPlanWaves>({keep && st == kHi, keep && st == kLo}, s_wave, rank, tot);
-    const int slot = keep ? nst[st] + rank[st] : 0;
-    const bool new_page = keep && (slot % kPage) == 0;
-    block_counts<2, kPlanWaves>({new_page && st == kHi, new_page && st == kLo}, s_wave, prank, np);
-    if (threadIdx.x == 0) {
+    uint32_t e[kPlanRounds];                       // tag or ring_act byte, then action and bits
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        unsigned base = 0u;
-        int granted = 0;
-        if (np[x] > 0) {
-          base = atomicAdd(&cv.status[2 + x], (unsigned)np[x]);
-          granted = base >= pool[x] ? 0 : (int)min((unsigned)np[x], pool[x] - base);
-        }
-        s_page_base[x] = base;
-        s_granted[x] = granted;
+    for (int r = 0; r < kPlanRounds; ++r) {
+      e[r] = 0u;
+      const int x = x0 + 64 * r;
+      if (r < rounds && x < n_x) {
+        if (kWindow && x < nr) e[r] = ract[(e0 + x) % W];
+        else if (tags) e[r] = tags[x - nr];
       }
     }
+    int2 wt = make_int2(0, 0);
+#pragma unroll
+    for (int r = 0; r < kPlanRounds; ++r) {
+      if (r < rounds) {
+        const int x = x0 + 64 * r;
+        if (!kWindow || x >= nr) {                   // a new token (past n_x: not looked at)
+          uint32_t t = s_tab[e[r]];
+          if (x < n_sunk) t = kHigh | kEntForced | (t & kEntBad);
+          if constexpr (kBudget) {
+            if (budget && x < n_x) t = (t & ~3u) | s_act[x - c0];
+          }
+          e[r] = t;
+          if (x < n_x && (t & kEntBad)) flags |= PASK_FLAG_BAD_TAG;
+        }
+        wt.x += __popcll(__ballot(x < n_out && (e[r] & 3u) == kHigh));
+        wt.y += __popcll(__ballot(x < n_out && (e[r] & 3u) == 1u));
+      }
+    }
+    if (lane == 0) s_wave[wave] = wt;
     __syncthreads();
+    int rank[2] = {0, 0}, tot[2] = {0, 0};
+#pragma unroll
+    for (int w = 0; w < kPlanWaves; ++w) {
+      const int2 c = s_wave[w];
+      rank[0] += w < wave ? c.x : 0;
+      rank[1] += w < wave ? c.y : 0;
+      tot[0] += c.x;
+      tot[1] += c.y;
+    }
     int pages_before[2];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) pages_before[x] = (nst[x] + kPage - 1) / kPage;
-    bool stored = false;
-    if (keep) {
-      const int pidx = slot / kPage;
-      stored = pidx < pages_before[st] + s_granted[st];
-      if (stored) {
-        if (new_page) bt[st][pidx] = (int)(s_page_base[st] + (unsigned)prank[st]);
-        il[st][slot] = pos;
-      } else {
-        flags |= st == kHi ? PASK_FLAG_HI_POOL_EXHAUSTED : PASK_FLAG_LO_POOL_EXHAUSTED;
+    for (int s = 0; s < 2; ++s) pages_before[s] = (nst[s] + kPage - 1) / kPage;
+    if (threadIdx.x < 2) {                         // the pages of the slots that open one
+      const int s = (int)threadIdx.x;
+      const int first = s ? nst[1] : nst[0], add = s ? tot[1] : tot[0];
+      const int opens = (first + add + kPage - 1) / kPage - (first + kPage - 1) / kPage;
+      const unsigned limit = s ? pool[1] : pool[0];
+      unsigned base = 0u;
+      int granted = 0;
+      if (opens > 0) {
+        base = atomicAdd(&cv.status[2 + s], (unsigned)opens);
+        granted = base >= limit ? 0 : (int)min((unsigned)opens, limit - base);
+      }
+      s_page_base[s] = base;
+      s_granted[s] = granted;
+    }
+    __syncthreads();
+    int cap[2], page0[2], next[2];                 // slots there is room for; page of slot s: page0 + s / 16
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      cap[s] = (pages_before[s] + s_granted[s]) * kPage;
+      page0[s] = (int)(s_page_base[s] - (unsigned)pages_before[s]);
+      next[s] = uni(nst[s] + rank[s]);             // next slot of this wave's tokens
+    }
+#pragma unroll
+    for (int r = 0; r < kPlanRounds; ++r) {
+      if (r < rounds) {
+        const int x = x0 + 64 * r;
+        const bool hi = x < n_out && (e[r] & 3u) == kHigh, lo = x < n_out && (e[r] & 3u) == 1u;
+        const unsigned long long mh = __ballot(hi), ml = __ballot(lo);
+        const int slot = hi ? next[0] + lanes_below(mh) : next[1] + lanes_below(ml);
+        if ((hi || lo) && slot < (hi ? cap[0] : cap[1])) {
+          il[hi ? slot : cv.max_tokens + slot] = e0 + x;
+          if (slot % kPage == 0)
+            bt[(hi ? 0 : cv.max_pages) + slot / kPage] = (hi ? page0[0] : page0[1]) + slot / kPage;
+          if (e[r] & kEntForced) ++c_forced;
+        }
+        next[0] += __popcll(mh);
+        next[1] += __popcll(ml);
+        if (kWindow && x >= nr && x >= n_out && x < n_x) ract[(e0 + x) % W] = (uint8_t)(e[r] & 7u);
       }
     }
-    if (valid) stg[j] = stored ? ((st << 30) | slot) : -1;
-    int unused[4], c[4];
-    block_counts<4, kPlanWaves>({fits && act == kDrop, stored && forced, valid && !stored && !(fits && act == kDrop),
-                                 fits},
-                                s_wave, unused, c);
 #pragma unroll
-    for (int x = 0; x < 2; ++x) nst[x] = min(nst[x] + tot[x], (pages_before[x] + s_granted[x]) * kPage);
-    n_drop += c[0];
-    n_forced += c[1];
-    n_lost += c[2];
-    n_fit += c[3];
+    for (int s = 0; s < 2; ++s) {
+      n_kept += tot[s];
+      if (nst[s] + tot[s] > cap[s]) {
+        n_lost += nst[s] + tot[s] - cap[s];
+        flags |= s == kHi ? PASK_FLAG_HI_POOL_EXHAUSTED : PASK_FLAG_LO_POOL_EXHAUSTED;
+      }
+      nst[s] = min(nst[s] + tot[s], cap[s]);
+    }
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) c_forced += __shfl_xor(c_forced, off);
+  if (lane == 0 && c_forced) atomicAdd(&s_forced, c_forced);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) flags |= (uint32_t)__shfl_xor((int)flags, off);
+  if (lane == 0 && flags) atomicOr(cv.status, flags);
+  __syncthreads();
   if (threadIdx.x == 0) {
     cnt[kCntHi] = nst[0];
     cnt[kCntLo] = nst[1];
-    cnt[kCntPos] = pos0 + n_fit;
-    cnt[kCntDrop] += n_drop;
-    cnt[kCntForced] += n_forced;
-    cnt[kCntLost] += n_lost;
+    cnt[kCntPos] = p0 + n_fit;
+    cnt[kCntDrop] = drop0 + n_out - n_kept;
+    cnt[kCntForced] = forced0 + s_forced;
+    cnt[kCntLost] = lost0 + n_lost + (n - n_fit);
     if (budget) *budget_of(cnt) = R;
   }
-  if (flags) atomicOr(cv.status, flags);
 }
 
 // ---------------------------------------------------------------------------
@@ -944,13 +1089,6 @@ __global__ __launch_bounds__(256) void append_step_kernel(AppendArgs a) {
 // pages of the HIGH pool reserved for the windows.  It is persisted by its
 // action when position p + W is appended.
 
-__device__ __forceinline__ int ring_page(const CacheView& cv, int b, int layer, int k) {
-  return (b * cv.n_layers + layer) * cv.ring_pp + k;
-}
-__device__ __forceinline__ uint8_t* ring_act_of(const CacheView& cv, int b, int layer) {
-  return cv.ring_act + ((size_t)b * cv.n_layers + layer) * cv.window;
-}
-
 // The bf16 K and V rows [Hkv][D] of slot t of a HIGH-layout page (the
 // inverse of write_hi), into kout / vout, by the whole block.
 template <int D>
@@ -973,165 +1111,6 @@ __device__ __forceinline__ void read_hi_token(const CacheView& cv, int page, int
         reinterpret_cast<const uint16_t*>(pg + (size_t)((g + page) % cv.n_kv_heads) * PL::kHiHead + PL::kHiV);
     vout[g * D + d] = src[(((m >> 1) * 64 + qq * 16 + dd) * 2 + (m & 1)) * 4 + jj];
   }
-}
-
-// Bulk append with a window.  The call's combined index x covers positions
-// q = e0 + x, e0 = max(0, p0 - W): first the window's tokens from before the
-// call (x < nr = p0 - e0; their decisions in ring_act), then the new tokens
-// (j = x - nr).  Positions below e1 = max(e0, p0 + n_fit - W) leave the window
-// now and are slotted into the stores in position order as in
-// append_plan_kernel; the new tokens from e1 on enter the window and their
-// decisions go to ring_act (after every read of ring_act in the chunk: the
-// W positions of the window after the call have distinct slots, so no slot
-// still in the window is overwritten).  staging[x] gets the store code of x
-// or -1; the sequence's last four staging words keep the stores' counts
-// before the call, p0 and n_fit for the pack (append_pack_page_kernel, which
-// reads a leaving window entry from its ring slot) and window-fill kernels.
-template <bool kBudget>
-__global__ __launch_bounds__(256) void append_plan_window_kernel(AppendArgs a) {
-  __shared__ uint8_t s_a0[64], s_amin[64];
-  __shared__ int s_wave[4];
-  __shared__ unsigned s_page_base[2];
-  __shared__ int s_granted[2];
-  struct Empty {};
-  __shared__ std::conditional_t<kBudget, BudgetTable, Empty> s_bud;
-  __shared__ uint8_t s_act[kBudget ? 256 : 1];
-  const CacheView& cv = a.cv;
-  const int b = blockIdx.x;
-  const int W = cv.window;
-  load_table(a.tab, s_a0, s_amin);
-  uint32_t flags = 0;
-  const int n = clamp_n_new(a, b, flags);
-  int32_t* cnt = counters_of(cv, b, a.layer);
-  const int p0 = cnt[kCntPos];
-  const int n_fit = max(0, min(n, cv.max_tokens - p0));
-  if (n_fit < n) flags |= PASK_FLAG_SEQ_CAPACITY;
-  const int e0 = max(0, p0 - W), nr = p0 - e0;
-  const int n_out = max(e0, p0 + n_fit - W) - e0;    // entries leaving the window now
-  const int n_x = nr + n_fit;
-  uint8_t* ract = ring_act_of(cv, b, a.layer);
-  bool budget = false;
-  int64_t R = 0;
-  if constexpr (kBudget) {
-    const uint4* src = reinterpret_cast<const uint4*>(cv.budget);
-    uint4* dst = reinterpret_cast<uint4*>(&s_bud);
-    for (int i = threadIdx.x; i < (int)(sizeof(BudgetTable) / 16); i += 256) dst[i] = src[i];
-    __syncthreads();
-    budget = s_bud.loaded == kBudgetLoaded;
-    if (!budget && threadIdx.x == 0) flags |= PASK_FLAG_NO_BUDGET;
-    if (budget && threadIdx.x == 0) R = *budget_of(cnt);
-  }
-  int nst[2] = {cnt[kCntHi], cnt[kCntLo]};
-  int n_drop = 0, n_forced = 0, n_lost = 0;
-  int32_t* bt[2] = {block_table_of(cv, b, a.layer, kHi), block_table_of(cv, b, a.layer, kLo)};
-  int32_t* il[2] = {index_list_of(cv, b, a.layer, kHi), index_list_of(cv, b, a.layer, kLo)};
-  int32_t* stg = cv.staging + (size_t)b * cv.staging_stride;
-  if (threadIdx.x == 0) {                          // for the pack kernel: the stores' counts before the call
-    stg[cv.staging_stride - 4] = nst[0];
-    stg[cv.staging_stride - 3] = nst[1];
-  }
-  const bool keep_all = (a.flags & kKeepAll) != 0u;
-  const unsigned pool[2] = {(unsigned)cv.hi_pages, (unsigned)cv.lo_pages};
-  __syncthreads();
-
-  for (int c0 = 0; c0 < n_x; c0 += 256) {
-    const int x = c0 + (int)threadIdx.x;
-    const bool valid = x < n_x;
-    const bool is_new = valid && x >= nr;
-    const int j = x - nr;
-    const int q = e0 + x;
-    if constexpr (kBudget) {
-      if (budget && threadIdx.x == 0) {              // the chunk's new tokens, in position order
-        const int j1 = min(n_fit, c0 + 256 - nr);
-        for (int jj = max(0, c0 - nr); jj < j1; ++jj) {
-          const size_t at = (size_t)b * a.max_new + jj;
-          const int tag = (int)a.tags[at];
-          const bool forced = (uint32_t)(p0 + jj) < s_bud.n_sink || (uint32_t)tag >= s_bud.n_tags;
-          s_act[jj + nr - c0] =
-              (uint8_t)budget_decide(&s_bud, tag, (int)a.states[at], forced, (int)a.tab.group, R, flags);
-        }
-      }
-      __syncthreads();
-    }
-    int act = kDrop;
-    bool forced = false, bad = false;
-    if (is_new) {
-      const int tag = a.tags ? (int)a.tags[(size_t)b * a.max_new + j] : 0;
-      act = decide(s_a0, s_amin, a.tab.n_tags, a.tab.n_sink, keep_all, tag, q, forced, bad);
-      if constexpr (kBudget) {
-        if (budget) act = s_act[threadIdx.x];
-      }
-    } else if (valid) {
-      const uint8_t byte = ract[q % W];
-      act = byte & 3;
-      forced = ((byte >> 2) & 1) != 0;
-    }
-    if (bad) flags |= PASK_FLAG_BAD_TAG;
-    const bool leaving = valid && x < n_out;
-    const int st = act == kHigh ? kHi : kLo;
-    const bool keep = leaving && act != kDrop;
-    int tot_hi, tot_lo, np_hi, np_lo;
-    const int r_hi = block_exclusive_count(keep && st == kHi, s_wave, tot_hi);
-    const int r_lo = block_exclusive_count(keep && st == kLo, s_wave, tot_lo);
-    const int slot = keep ? nst[st] + (st == kHi ? r_hi : r_lo) : 0;
-    const bool new_page = keep && (slot % kPage) == 0;
-    const int pr_hi = block_exclusive_count(new_page && st == kHi, s_wave, np_hi);
-    const int pr_lo = block_exclusive_count(new_page && st == kLo, s_wave, np_lo);
-    if (threadIdx.x == 0) {
-      const int np[2] = {np_hi, np_lo};
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-        unsigned base = 0u;
-        int granted = 0;
-        if (np[y] > 0) {
-          base = atomicAdd(&cv.status[2 + y], (unsigned)np[y]);
-          granted = base >= pool[y] ? 0 : (int)min((unsigned)np[y], pool[y] - base);
-        }
-        s_page_base[y] = base;
-        s_granted[y] = granted;
-      }
-    }
-    __syncthreads();                                 // also: every read of ract in this chunk is done
-    int pages_before[2];
-#pragma unroll
-    for (int y = 0; y < 2; ++y) pages_before[y] = (nst[y] + kPage - 1) / kPage;
-    bool stored = false;
-    if (keep) {
-      const int pidx = slot / kPage;
-      stored = pidx < pages_before[st] + s_granted[st];
-      if (stored) {
-        if (new_page) bt[st][pidx] = (int)(s_page_base[st] + (unsigned)(st == kHi ? pr_hi : pr_lo));
-        il[st][slot] = q;
-      } else {
-        flags |= st == kHi ? PASK_FLAG_HI_POOL_EXHAUSTED : PASK_FLAG_LO_POOL_EXHAUSTED;
-      }
-    }
-    if (valid) stg[x] = stored ? ((st << 30) | slot) : -1;
-    if (is_new && !leaving) ract[q % W] = (uint8_t)(act | (forced ? 4 : 0));
-    int c_drop, c_forced, c_lost;
-    block_exclusive_count(leaving && act == kDrop, s_wave, c_drop);
-    block_exclusive_count(stored && forced, s_wave, c_forced);
-    block_exclusive_count(keep && !stored, s_wave, c_lost);
-    const int tot[2] = {tot_hi, tot_lo};
-#pragma unroll
-    for (int y = 0; y < 2; ++y) nst[y] = min(nst[y] + tot[y], (pages_before[y] + s_granted[y]) * kPage);
-    n_drop += c_drop;
-    n_forced += c_forced;
-    n_lost += c_lost;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    cnt[kCntHi] = nst[0];
-    cnt[kCntLo] = nst[1];
-    cnt[kCntPos] = p0 + n_fit;
-    cnt[kCntDrop] += n_drop;
-    cnt[kCntForced] += n_forced;
-    cnt[kCntLost] += n_lost + (n - n_fit);
-    if (budget) *budget_of(cnt) = R;
-    stg[cv.staging_stride - 2] = p0;
-    stg[cv.staging_stride - 1] = n_fit;
-  }
-  if (flags) atomicOr(cv.status, flags);
 }
 
 // The new tokens that stay in the window (the last min(n_fit, W) of the
@@ -1231,8 +1210,8 @@ hipError_t launch_budget_init(const CacheView& cv, int32_t batch, int64_t r0, hi
 hipError_t launch_append(const AppendArgs& a, hipStream_t s) {
   if (a.max_new == 1 && a.n_new == nullptr) return launch_append_step(a, s);
   if (a.cv.window > 0) {
-    if (a.states) append_plan_window_kernel<true><<<dim3(a.batch), dim3(256), 0, s>>>(a);
-    else append_plan_window_kernel<false><<<dim3(a.batch), dim3(256), 0, s>>>(a);
+    if (a.states) append_plan_kernel<true, true><<<dim3(a.batch), dim3(kPlanThreads), 0, s>>>(a);
+    else append_plan_kernel<false, true><<<dim3(a.batch), dim3(kPlanThreads), 0, s>>>(a);
     // pages of a store this call's leaving entries (at most max_new + W) can reach
     const dim3 gp((a.max_new + a.cv.window + kPage - 1) / kPage + 1, 2, a.batch);
     const dim3 gf((std::min(a.max_new, a.cv.window) + kPackTokens - 1) / kPackTokens, a.batch);
@@ -1245,8 +1224,8 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t s) {
     }
     return hipGetLastError();
   }
-  if (a.states) append_plan_kernel<true><<<dim3(a.batch), dim3(kPlanThreads), 0, s>>>(a);
-  else append_plan_kernel<false><<<dim3(a.batch), dim3(kPlanThreads), 0, s>>>(a);
+  if (a.states) append_plan_kernel<true, false><<<dim3(a.batch), dim3(kPlanThreads), 0, s>>>(a);
+  else append_plan_kernel<false, false><<<dim3(a.batch), dim3(kPlanThreads), 0, s>>>(a);
   // pages of a store one sequence's slots of this call can reach: ceil(max_new / 16) + 1
   const dim3 grid((a.max_new + kPage - 1) / kPage + 1, 2, a.batch);
   if (a.cv.head_dim == 64) append_pack_page_kernel<64><<<grid, dim3(kPackThreads), 0, s>>>(a);
