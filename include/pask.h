@@ -164,7 +164,8 @@ typedef struct pask_cache_layout {
                                 store 0 = HIGH, 1 = LOW                            */
   uint64_t index_list_off;   /* i32 [max_batch][n_layers][2][max_tokens_per_seq]:
                                 position of each slot of each store               */
-  uint64_t staging_off;      /* i32 [max_batch][staging_stride]: append plan       */
+  uint64_t staging_off;      /* i32 [max_batch][staging_stride]: a bulk append's
+                                scratch (its last four words are used)             */
   uint64_t budget_off;       /* the online controller's tables (pask_budget_init)  */
   uint64_t ring_act_off;     /* u8 [max_batch][n_layers][W]: decided action | forced
                                 << 2 of the token in each recent-window slot       */
@@ -325,7 +326,7 @@ size_t pask_workspace_bytes(const pask_geom* geom, int32_t batch, int32_t max_ct
  *   lse_dev[b][h] = natural-log sum-exp of the scaled scores (fp32; nullable)
  * The history is the persisted entries plus the recent window (bf16).  A
  * sequence with no visible entry gives out = 0 and lse = -inf.
- * With a new token, at most 256 sequences, no recent window and no parser
+ * With a new token, at most 1024 sequences, no recent window and no parser
  * states, the attention kernels persist the tokens themselves (one launch
  * fewer): the pages the call opens are then granted in sequence order (where
  * a pool runs out, the lower sequences get its last pages), where the

@@ -396,53 +396,49 @@ __device__ __forceinline__ void attend_pair(const Raw& xa, const Raw& xb, AttnSt
 // compiler treats what depends on it as uniform.
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+// Inclusive prefix sum and maximum over the 64 lanes (values >= 0), by DPP row
+// shifts and row broadcasts: vector moves of a few cycles each, where a lane
+// shuffle is a round trip through LDS; every wave of the attention kernel
+// runs them in series with its first loads.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int dpp_or_zero(int x) {   // lanes without a source get 0
+  return __builtin_amdgcn_update_dpp(0, x, kCtrl, kRows, 0xF, false);
+}
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
+  x += dpp_or_zero<0x111, 0xF>(x);                 // row_shr:1, 2, 4, 8 within each row of 16
+  x += dpp_or_zero<0x112, 0xF>(x);
+  x += dpp_or_zero<0x114, 0xF>(x);
+  x += dpp_or_zero<0x118, 0xF>(x);
+  x += dpp_or_zero<0x142, 0xA>(x);                 // row_bcast:15 into rows 1 and 3
+  x += dpp_or_zero<0x143, 0xC>(x);                 // row_bcast:31 into rows 2 and 3
   return x;
 }
 __device__ __forceinline__ int wave_max(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x = max(x, __shfl_xor(x, off));
-  return x;
-}
-__device__ __forceinline__ int wave_inclusive_scan(int x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
-  return x;
+  x = max(x, dpp_or_zero<0x111, 0xF>(x));
+  x = max(x, dpp_or_zero<0x112, 0xF>(x));
+  x = max(x, dpp_or_zero<0x114, 0xF>(x));
+  x = max(x, dpp_or_zero<0x118, 0xF>(x));
+  x = max(x, dpp_or_zero<0x142, 0xA>(x));
+  x = max(x, dpp_or_zero<0x143, 0xC>(x));
+  return __builtin_amdgcn_readlane(x, 63);
 }
 
 __device__ __forceinline__ int window_slots(const AttnArgs& a, int n_pos) { return min(n_pos, a.cv.window); }
 
-// Store counts of sequence `lane` for the first 64 sequences, read once per
-// block: the plan, the search for a block's first sequence and the walk to
-// the next sequence take them from registers instead of memory.
-// A call that persists its step's entries plans with counts that differ
-// from the counters: those of every sequence (n_hi, n_win, n_lo, n_x as four
-// ints) are then at more[b * stride], for the sequences beyond the first 64.
-struct FirstCounts {
-  int n_hi, n_lo, n_win;   // 0 past the batch
-  int n_x;                 // 1 when the call persists and attends an entry of the sequence
-  const int32_t* more;     // null: the counters
-  int stride;
+// What a workgroup plans with: the store counts of every sequence below n_lds
+// in LDS, as (n_hi, n_win, n_lo, n_x), n_x = 1 when the call persists and
+// attends an entry of the sequence; those of further sequences (only in calls
+// that persist nothing) are read from the counters.  incl: the units of each
+// sequence and the lower ones of its chunk of 64; chunk: each chunk's units
+// and its longest sequence's.  A workgroup of one wave keeps its only chunk's
+// in registers instead (lane = sequence).
+struct CallCounts {
+  const int4* lds;
+  int n_lds;
+  const int* incl;
+  const int2* chunk;
+  int lane_incl, lane_len;
 };
-__device__ __forceinline__ FirstCounts first_counts(const AttnArgs& a) {
-  const int lane = threadIdx.x & 63;
-  const int32_t* c = counters_of(a.cv, lane < a.batch ? lane : 0, a.layer);
-  const int hi = c[kCntHi], lo = c[kCntLo], pos = c[kCntPos];
-  FirstCounts f;
-  f.n_hi = lane < a.batch ? hi : 0;
-  f.n_lo = lane < a.batch ? lo : 0;
-  f.n_win = lane < a.batch ? window_slots(a, pos) : 0;
-  f.n_x = 0;
-  f.more = nullptr;
-  f.stride = 0;
-  return f;
-}
 
 // ---------------------------------------------------------------------------
 // the step's new entry, persisted by the attention call itself
@@ -456,148 +452,158 @@ struct EntryRecord {
 };
 constexpr int kEntStored = 4, kEntForced = 8, kEntOpens = 16, kEntCapacity = 32;
 
-// The one-token append's rules (decide, then the next slot of the entry's
-// store, a new page when that slot opens one), with the pages a call opens
-// granted in sequence order from the pool cursors rather than by atomics, so
-// that every worker computes the same outcome for every sequence from the
-// cache as it stands when the call starts.  Lane l takes sequence b = c0 + l
-// of a chunk of 64 (n_hi, n_lo, pos: its counters; opened_*: the pages the
-// sequences of earlier chunks open, advanced past this chunk's); s_a0 /
-// s_amin: Lambda's column.
-__device__ __forceinline__ EntryRecord predict_entry(const AttnArgs& a, const uint8_t* s_a0, const uint8_t* s_amin,
-                                                     int b, int n_hi, int n_lo, int pos, uint32_t& opened_hi,
-                                                     uint32_t& opened_lo) {
+// The counts a workgroup of kWaves waves plans with, into s_cnt, by all of
+// them: wave wv takes the sequences of chunks wv, wv + kWaves, ... of 64, one
+// per lane, every load issued before the first is used.  A call that persists
+// its step's entries (a.tags_new) also decides them (decide, then the next
+// slot of the entry's store, a new page when that slot opens one), with the
+// pages the call opens granted in sequence order from the pool cursors rather
+// than by atomics, so that every workgroup computes the same outcome for every
+// sequence from the cache as it stands when the call starts; s_ent[b] gets it.
+// s_open: the pages each chunk opens (HIGH, LOW).  s_a0 / s_amin: Lambda's
+// column.  The four waves share one plan, so that 1,024 sequences fit where a
+// plan per wave held 256 and each wave decides a quarter: a call of 384
+// sequences (prompts of 64-768 tokens, 8 KV heads, D 128) went from 6.2 us of
+// one-token append and 132.0 us of attention to 133.9 us for both.
+template <int kWaves, int kSeq, bool kEntries>     // sequences s_cnt and s_ent hold; the call may persist entries
+__device__ __forceinline__ CallCounts plan_counts(const AttnArgs& a, const uint8_t* s_a0, const uint8_t* s_amin,
+                                                  EntryRecord* s_ent, int4* s_cnt, int* s_incl, int2* s_open,
+                                                  int2* s_chunk) {
+  constexpr int kC = kSeq / 64 / kWaves;           // chunks of one wave
+  static_assert(kC * 64 * kWaves == kSeq, "whole chunks");
   const CacheView& cv = a.cv;
-  const bool live = b < a.batch;
-  const int tag = live ? (int)a.tags_new[b] : 0;
-  uint32_t flags = 0u;
-  bool forced = false, bad = false, opens = false, stored = false;
-  int act = kDrop, store = kHi, slot = 0, page = -1;
-  const bool cap = pos >= cv.max_tokens;
-  if (cap) {
-    flags |= PASK_FLAG_SEQ_CAPACITY;
-  } else {
-    act = decide(s_a0, s_amin, a.tab.n_tags, a.tab.n_sink, false, tag, pos, forced, bad);
-    if (bad) flags |= PASK_FLAG_BAD_TAG;
-    if (act != kDrop) {
-      store = act == kHigh ? kHi : kLo;
-      slot = store == kHi ? n_hi : n_lo;
-      opens = slot % kPage == 0;
-      stored = !opens;
-    }
-  }
-  const unsigned long long open_hi = __ballot(live && opens && store == kHi);
-  const unsigned long long open_lo = __ballot(live && opens && store == kLo);
-  if (live && opens) {
-    const unsigned long long m = store == kHi ? open_hi : open_lo;
-    const uint32_t before = (store == kHi ? opened_hi : opened_lo) +
-                            __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    const uint32_t pid = cv.status[2 + store] + before;
-    const uint32_t pool = store == kHi ? (uint32_t)cv.hi_pages : (uint32_t)cv.lo_pages;
-    if (pid < pool) {
-      page = (int)pid;
-      stored = true;
-    } else {
-      flags |= store == kHi ? PASK_FLAG_HI_POOL_EXHAUSTED : PASK_FLAG_LO_POOL_EXHAUSTED;
-    }
-  }
-  opened_hi += (uint32_t)__popcll(open_hi);       // the lower sequences' page openings, in later chunks
-  opened_lo += (uint32_t)__popcll(open_lo);
-  EntryRecord r;
-  r.word = act | (stored ? kEntStored : 0) | (forced ? kEntForced : 0) | (opens ? kEntOpens : 0) |
-           (cap ? kEntCapacity : 0) | (int)(flags << 8);
-  r.slot = slot;
-  r.page = page;
-  r.pos = pos;
-  return r;
-}
-
-// First counts of a call that persists its step's entries (at most
-// kFusedMaxBatch sequences, no recent window): the stores as they stand, plus
-// the entry of each sequence that gets stored (n_x).  Every sequence's counts
-// go to cnt[b] and its entry's outcome to ent[b]; the first 64 also stay in
-// registers.
-template <int kSeq>                                // the sequences ent and cnt hold (>= batch)
-__device__ __forceinline__ FirstCounts first_counts_entry(const AttnArgs& a, const uint8_t* s_a0,
-                                                          const uint8_t* s_amin, EntryRecord* ent, int4* cnt) {
-  const int lane = threadIdx.x & 63;
-  uint32_t opened_hi = 0u, opened_lo = 0u;
-  FirstCounts f;
+  const int lane = threadIdx.x & 63, wv = (int)(threadIdx.x >> 6);
+  const int n_lds = min(a.batch, kSeq);
+  const bool fused = kEntries && a.tags_new != nullptr;
+  int hi[kC], lo[kC], pos[kC], tag[kC];
 #pragma unroll
-  for (int c0 = 0; c0 < kSeq; c0 += 64) {
-    if (c0 > 0 && c0 >= a.batch) break;
-    const int b = c0 + lane;
-    const int32_t* c = counters_of(a.cv, b < a.batch ? b : 0, a.layer);
-    const int hi = c[kCntHi], lo = c[kCntLo], pos = c[kCntPos];
-    const EntryRecord r = predict_entry(a, s_a0, s_amin, b, hi, lo, pos, opened_hi, opened_lo);
-    const bool live = b < a.batch;
-    const int4 k = live ? make_int4(hi, 0, lo, (r.word & kEntStored) ? 1 : 0) : make_int4(0, 0, 0, 0);
-    ent[b] = r;
-    cnt[b] = k;
-    if (c0 == 0) {
-      f.n_hi = k.x;
-      f.n_win = 0;
-      f.n_lo = k.z;
-      f.n_x = k.w;
+  for (int i = 0; i < kC; ++i) {
+    const int b = (wv + i * kWaves) * 64 + lane;
+    hi[i] = lo[i] = pos[i] = tag[i] = 0;
+    if (b < n_lds) {
+      const int32_t* c = counters_of(cv, b, a.layer);
+      hi[i] = c[kCntHi];
+      lo[i] = c[kCntLo];
+      pos[i] = c[kCntPos];
+      if (fused) tag[i] = (int)a.tags_new[b];
     }
   }
-  f.more = reinterpret_cast<const int32_t*>(cnt);
-  f.stride = 4;
-  return f;
-}
-// The merge kernels of such a call take the counts the attention kernel
-// planned with from the workspace (the counters change under them: the
-// merge kernel also enters the entries).
-__device__ __forceinline__ FirstCounts planned_counts(const AttnArgs& a) {
-  if (!a.tags_new) return first_counts(a);
-  const int lane = threadIdx.x & 63;
-  const int4 r = lane < a.batch ? *reinterpret_cast<const int4*>(a.ws_seq + lane * 8) : make_int4(0, 0, 0, 0);
-  FirstCounts f;
-  f.n_hi = r.x;
-  f.n_win = r.y;
-  f.n_lo = r.z;
-  f.n_x = r.w;
-  f.more = a.ws_seq;
-  f.stride = 8;
+  CallCounts f{s_cnt, n_lds, s_incl, s_chunk, 0, 0};
+  auto counted = [&](int chunk, const int4& c) {   // the counts of sequence 64 chunk + lane (0 past the batch)
+    const int len = len_of(c.x, c.y, c.z, c.w), incl = wave_inclusive_scan(len);
+    s_cnt[chunk * 64 + lane] = c;
+    if constexpr (kWaves == 1) {
+      f.lane_incl = incl;
+      f.lane_len = len;
+    } else {
+      s_incl[chunk * 64 + lane] = incl;
+      const int longest = wave_max(len);
+      if (lane == 63) s_chunk[chunk] = make_int2(incl, longest);
+    }
+  };
+  if (!fused) {
+#pragma unroll
+    for (int i = 0; i < kC; ++i)
+      if ((wv + i * kWaves) * 64 < n_lds)
+        counted(wv + i * kWaves, make_int4(hi[i], window_slots(a, pos[i]), lo[i], 0));
+    if (kWaves > 1) __syncthreads();
+    return f;
+  }
+  const uint32_t cursor[2] = {cv.status[2], cv.status[3]};
+  int word[kC], rank[kC];                          // rank: pages the chunk's lower sequences open in the same pool
+#pragma unroll
+  for (int i = 0; i < kC; ++i) {
+    const int c0 = (wv + i * kWaves) * 64, b = c0 + lane;
+    word[i] = rank[i] = 0;
+    if (c0 >= n_lds) continue;                     // wave-uniform
+    const bool live = b < n_lds;
+    uint32_t flags = 0u;
+    bool forced = false, bad = false, opens = false, stored = false;
+    int act = kDrop;
+    const bool cap = pos[i] >= cv.max_tokens;
+    if (cap) {
+      flags |= PASK_FLAG_SEQ_CAPACITY;
+    } else {
+      act = decide(s_a0, s_amin, a.tab.n_tags, a.tab.n_sink, false, tag[i], pos[i], forced, bad);
+      if (bad) flags |= PASK_FLAG_BAD_TAG;
+      if (act != kDrop) {
+        opens = (act == kHigh ? hi[i] : lo[i]) % kPage == 0;
+        stored = !opens;
+      }
+    }
+    const unsigned long long open_hi = __ballot(live && opens && act == kHigh);
+    const unsigned long long open_lo = __ballot(live && opens && act != kHigh);
+    const unsigned long long m = act == kHigh ? open_hi : open_lo;
+    rank[i] = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    word[i] = act | (stored ? kEntStored : 0) | (forced ? kEntForced : 0) | (opens ? kEntOpens : 0) |
+              (cap ? kEntCapacity : 0) | (int)(flags << 8);
+    if (lane == 0) s_open[wv + i * kWaves] = make_int2(__popcll(open_hi), __popcll(open_lo));
+  }
+  if (kWaves > 1) __syncthreads();
+  int2 before[kC];                                 // pages the chunks before this one open
+#pragma unroll
+  for (int i = 0; i < kC; ++i) before[i] = make_int2(0, 0);
+  if (kWaves > 1) {
+    const int n_chunks = (n_lds + 63) / 64;
+    for (int c = 0; c + 1 < n_chunks; ++c) {
+      const int2 o = s_open[c];
+#pragma unroll
+      for (int i = 0; i < kC; ++i) {
+        before[i].x += c < wv + i * kWaves ? o.x : 0;
+        before[i].y += c < wv + i * kWaves ? o.y : 0;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kC; ++i) {
+    const int c0 = (wv + i * kWaves) * 64, b = c0 + lane;
+    if (c0 >= n_lds) continue;
+    const int store = (word[i] & 3) == kHigh ? kHi : kLo;
+    EntryRecord r;
+    r.word = word[i];
+    r.slot = (word[i] & 3) == kDrop ? 0 : (store == kHi ? hi[i] : lo[i]);
+    r.page = -1;
+    r.pos = pos[i];
+    if (word[i] & kEntOpens) {
+      const uint32_t pid = cursor[store] + (uint32_t)((store == kHi ? before[i].x : before[i].y) + rank[i]);
+      const uint32_t pool = store == kHi ? (uint32_t)cv.hi_pages : (uint32_t)cv.lo_pages;
+      if (pid < pool) {
+        r.page = (int)pid;
+        r.word |= kEntStored;
+      } else {
+        r.word |= (int)((store == kHi ? PASK_FLAG_HI_POOL_EXHAUSTED : PASK_FLAG_LO_POOL_EXHAUSTED) << 8);
+      }
+    }
+    s_ent[b] = r;
+    counted(wv + i * kWaves,
+            b < n_lds ? make_int4(hi[i], 0, lo[i], (r.word & kEntStored) ? 1 : 0) : make_int4(0, 0, 0, 0));
+  }
+  if (kWaves > 1) __syncthreads();
   return f;
 }
 
 // Pages of sequence b (wave-uniform, < batch).
-__device__ __forceinline__ SeqPages seq_pages(const AttnArgs& a, const FirstCounts& f, int b) {
-  if (b < 64)
-    return make_pages(__builtin_amdgcn_readlane(f.n_hi, b), __builtin_amdgcn_readlane(f.n_win, b),
-                      __builtin_amdgcn_readlane(f.n_lo, b), __builtin_amdgcn_readlane(f.n_x, b));
-  if (f.more) {
-    const int4 c = *reinterpret_cast<const int4*>(f.more + (size_t)b * f.stride);
+__device__ __forceinline__ SeqPages seq_pages(const AttnArgs& a, const CallCounts& f, int b) {
+  if (b < f.n_lds) {
+    const int4 c = f.lds[b];
     return make_pages(uni(c.x), uni(c.y), uni(c.z), uni(c.w));
   }
   const int32_t* c = counters_of(a.cv, b, a.layer);
   return make_pages(uni(c[kCntHi]), uni(window_slots(a, c[kCntPos])), uni(c[kCntLo]));
 }
-// The same from a wave's copy of the counts in LDS (sequence b's at c[b] for
-// b < n_lds), so that the walk over sequences keeps no registers for them.
-__device__ __forceinline__ SeqPages seq_pages(const AttnArgs& a, const int4* c_lds, int n_lds, int b) {
-  if (b < n_lds) {
-    const int4 c = c_lds[b];
-    return make_pages(uni(c.x), uni(c.y), uni(c.z), uni(c.w));
+// Length in units of sequence b (a lane's own; 0 past the batch).
+__device__ __forceinline__ int lane_len(const AttnArgs& a, const CallCounts& f, int b) {
+  if (b < f.n_lds) {
+    const int4 c = f.lds[b];
+    return len_of(c.x, c.y, c.z, c.w);
   }
+  if (b >= a.batch) return 0;
   const int32_t* c = counters_of(a.cv, b, a.layer);
-  return make_pages(uni(c[kCntHi]), uni(window_slots(a, c[kCntPos])), uni(c[kCntLo]));
+  return len_of(c[kCntHi], window_slots(a, c[kCntPos]), c[kCntLo]);
 }
-// Length in units of sequence c0 + lane (c0 wave-uniform; 0 past `limit`).
-__device__ __forceinline__ int lane_len(const AttnArgs& a, const FirstCounts& f, int c0, int limit) {
-  const int b = c0 + (int)(threadIdx.x & 63);
-  if (c0 == 0) return b < limit ? len_of(f.n_hi, f.n_win, f.n_lo, f.n_x) : 0;
-  if (f.more) {
-    const int4 r = b < limit ? *reinterpret_cast<const int4*>(f.more + (size_t)b * f.stride) : make_int4(0, 0, 0, 0);
-    return len_of(r.x, r.y, r.z, r.w);
-  }
-  const int32_t* c = counters_of(a.cv, b < a.batch ? b : 0, a.layer);
-  const int len = len_of(c[kCntHi], window_slots(a, c[kCntPos]), c[kCntLo]);
-  return b < limit ? len : 0;
-}
-// The work split of a call (pask_plan.h) from its counts: every block of the
-// attention, merge and distortion kernels computes the same plan.
+// The work split of a call (pask_plan.h) from its counts: every wave of the
+// attention kernel computes the same plan; the worker that attends a segment's
+// last page leaves the segment's number of pieces for the merge.
 constexpr int kWpb = PASK_ATTN_WPB;   // workers (waves) per workgroup of the weighted attention kernel
 using WeightedPlan = StreamPlan<kWpb>;
 constexpr int kMinPagesPerBlock = kUnitTokens / kPage;   // 8 pages: the workspace's piece size
@@ -608,55 +614,74 @@ constexpr int kSmallMinPages = 4;
 static_assert(PASK_SMALL_PIECES >= 1, "pieces per segment");
 static_assert(PASK_ODD_WEIGHT >= 1 && PASK_ODD_WEIGHT <= 16, "odd-XCD worker weight out of range");
 
-__device__ __forceinline__ void call_totals(const AttnArgs& a, const FirstCounts& f, long long& total, int& mx) {
-  int t = 0, m = 0;
-  for (int c0 = 0; c0 < a.batch; c0 += 64) {
-    const int len = lane_len(a, f, c0, a.batch);
-    t += uni(wave_sum(len));
-    m = max(m, uni(wave_max(len)));
+// The units of the whole call (one KV head), its longest sequence's, and the
+// units of chunk `lane` and the lower ones (a workgroup of one wave: of
+// sequence `lane` and the lower ones).
+template <bool kWeighted>
+__device__ __forceinline__ void call_totals(const AttnArgs& a, const CallCounts& f, int& total, int& mx, int& incl) {
+  const int lane = threadIdx.x & 63;
+  if constexpr (!kWeighted) {
+    incl = f.lane_incl;
+    total = __builtin_amdgcn_readlane(incl, 63);
+    mx = wave_max(f.lane_len);
+  } else {
+    const int2 c = lane < (f.n_lds + 63) / 64 ? f.chunk[lane] : make_int2(0, 0);
+    incl = wave_inclusive_scan(c.x);
+    total = __builtin_amdgcn_readlane(incl, 63);
+    mx = wave_max(c.y);
+    for (int c0 = f.n_lds; c0 < a.batch; c0 += 64) {   // n_lds is a multiple of 64 here
+      const int len = lane_len(a, f, c0 + lane);
+      total += __builtin_amdgcn_readlane(wave_inclusive_scan(len), 63);
+      mx = max(mx, wave_max(len));
+    }
   }
-  total = (long long)t * a.cv.n_kv_heads;
-  mx = m;
-}
-__device__ __forceinline__ WeightedPlan stream_plan(const AttnArgs& a, const FirstCounts& f, int n_blocks) {
-  long long total;
-  int mx;
-  call_totals(a, f, total, mx);
-  return stream_plan_of<kWpb>(total, mx, a.splits, a.min_pages, n_blocks, PASK_ODD_WEIGHT);
-}
-__device__ __forceinline__ EvenPlan even_plan(const AttnArgs& a, const FirstCounts& f, int n_blocks) {
-  long long total;
-  int mx;
-  call_totals(a, f, total, mx);
-  return even_plan_of(total, mx, min(a.splits, PASK_SMALL_PIECES + 1), a.min_pages, n_blocks);
 }
 template <typename Plan>
-__device__ __forceinline__ Plan make_plan(const AttnArgs& a, const FirstCounts& f, int n_blocks) {
-  if constexpr (std::is_same<Plan, EvenPlan>::value) return even_plan(a, f, n_blocks);
-  else return stream_plan(a, f, n_blocks);
+__device__ __forceinline__ Plan make_plan(const AttnArgs& a, int total, int mx) {
+  const long long units = (long long)total * a.cv.n_kv_heads;
+  if constexpr (std::is_same<Plan, EvenPlan>::value)
+    return even_plan_of(units, mx, min(a.splits, PASK_SMALL_PIECES + 1), a.min_pages, a.attn_blocks);
+  else
+    return stream_plan_of<kWpb>(units, mx, a.splits, a.min_pages, a.attn_blocks, PASK_ODD_WEIGHT);
 }
 
-// Sequence whose segments hold unit P, and the units of the sequences before it.
-__device__ __forceinline__ void locate(const AttnArgs& a, const FirstCounts& f, long long P, int& b_out,
-                                       int& excl_out) {
+// Sequence whose segments hold unit P < the call's units (incl: call_totals'),
+// its pages, and the units of the sequences before it.  A sequence without a
+// page adds nothing to the running sums, so the first sum past P is the
+// sequence's own.
+template <bool kWeighted>
+__device__ __forceinline__ void locate(const AttnArgs& a, const CallCounts& f, int incl, long long P, int& b_out,
+                                       SeqPages& sp, int& excl_out) {
   const long long H = a.cv.n_kv_heads;
-  int base = 0;
-  b_out = -1;
-  excl_out = 0;
-  for (int c0 = 0; c0 < a.batch; c0 += 64) {
-    const int len = lane_len(a, f, c0, a.batch);
-    const int incl = wave_inclusive_scan(len) + base;
-    const int excl = incl - len;
-    const bool hit = len > 0 && (long long)excl * H <= P && P < (long long)incl * H;
-    const unsigned long long m = __ballot(hit);
-    if (m) {
-      const int src = __ffsll((long long)m) - 1;
-      b_out = uni(c0 + src);
-      excl_out = uni(__shfl(excl, src));
-      return;
+  const int lane = threadIdx.x & 63;
+  int b = -1, upto = 0;                            // upto: units through sequence b
+  auto first_past = [&](int sum, int c0) -> bool {
+    const unsigned long long m = __ballot(P < (long long)sum * H);
+    if (!m) return false;
+    const int src = __ffsll((long long)m) - 1;
+    b = c0 + src;
+    upto = __builtin_amdgcn_readlane(sum, src);
+    return true;
+  };
+  if constexpr (!kWeighted) {
+    first_past(incl, 0);
+  } else {
+    if (first_past(incl, 0)) {                     // the chunk
+      const int c = b, base = c > 0 ? __builtin_amdgcn_readlane(incl, c - 1) : 0;
+      first_past(f.incl[c * 64 + lane] + base, c * 64);
+    } else {
+      int base = __builtin_amdgcn_readlane(incl, 63);
+      for (int c0 = f.n_lds; c0 < a.batch; c0 += 64) {
+        const int sum = wave_inclusive_scan(lane_len(a, f, c0 + lane)) + base;
+        if (first_past(sum, c0)) break;
+        base = __builtin_amdgcn_readlane(sum, 63);
+      }
     }
-    base = uni(__shfl(incl, 63));
   }
+  b_out = b;
+  if (b < 0) return;
+  sp = seq_pages(a, f, b);
+  excl_out = upto - sp.len;
 }
 
 // Stream pages [p0, p1) of one store of (b, g), loading page p+1 while
@@ -884,9 +909,20 @@ __device__ __forceinline__ void attend_entry(const AttnArgs& a, const EntryRecor
   attend_page<D, G, false, true>(xl, st, 1, a.scale_log2, q);
 }
 
+// Pieces of segment (b, g), for the merge kernels: 8 u16 per sequence at the
+// start of its workspace record (at most one piece per worker, so they fit),
+// written by the worker with the segment's last piece, or 0 for a sequence
+// without a page by the first workgroup.  While every merge block took the plan
+// anew from all sequences' counts, the merge kernel took 24.6 us at 384
+// sequences, 16.8 at 128 (8 query heads per KV head), 8.8 at 64 and 5.6 at one
+// (8 KV heads, D 128); it takes 10.3, 9.7, 5.9 and 4.6 us from the count.
+__device__ __forceinline__ uint16_t& pieces_of(const AttnArgs& a, int b, int g) {
+  return reinterpret_cast<uint16_t*>(a.ws_seq + (size_t)b * 8)[g];
+}
+
 // Pages [j0, j1) of (b, g) (HIGH store, recent window, LOW store): this
 // piece's partial of (b, g), combined with the others by attn_merge.
-template <int D, int G, typename Plan>
+template <int D, int G, bool kEntries, typename Plan>
 __device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, int g, int j0, int j1, const SeqPages& sp,
                                                long long seg0, const Plan& plan, int q, int n,
                                                const EntryRecord* ent) {
@@ -894,7 +930,7 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, 
   const CacheView& cv = a.cv;
   const int H = cv.n_kv_heads;
   EntryRows<D> rows;                               // the step's entry, attended last: its rows now
-  if (j1 > sp.np_l) {
+  if (kEntries && j1 > sp.np_l) {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(
         ((threadIdx.x & 63) < 32 ? a.k_new : a.v_new) + ((size_t)b * H + g) * D);
     const int l = threadIdx.x & 31;                // [K; V]: lanes 0-31 K, 32-63 V
@@ -936,7 +972,7 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, 
   if (l0 < l1)
     run_pages<D, G, false>(cv.lo_pool, cv.lo_page_bytes, PL::kLoHead, H, block_table_of(cv, b, a.layer, kLo), 0,
                            l0 - sp.np_w, l1 - sp.np_w, sp.n_lo, g, st, a.scale_log2, q, n, code_offsets);
-  if (j1 > sp.np_l) {                            // the step's entry (only when the call persists it)
+  if (kEntries && j1 > sp.np_l) {                // the step's entry (only when the call persists it)
     const EntryRecord er = ent[b];
     LoRaw<D> xl;
     prepare_entry<D>(a, b, g, er, q, n, xl, rows);
@@ -950,6 +986,8 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, 
   constexpr int G4 = G > 4 ? G : 4;
   const float l_n = head_sum(st.l);              // head n, over all slots
   const int slot = (int)(w - plan.block_of(seg0));   // < a.splits by the choice of range sizes
+  if (j1 == sp.np && (threadIdx.x & 63) == 0)       // the segment's last piece: their number, for the merge
+    pieces_of(a, b, g) = (uint16_t)max(1, min(slot + 1, a.splits));
   if (slot < 0 || slot >= a.splits) {            // never expected: report it, write nothing
     if ((threadIdx.x & 63) == 0) atomicOr(a.cv.status, (uint32_t)PASK_FLAG_WORKSPACE);
     return;
@@ -967,48 +1005,48 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, 
 
 // kWeighted: workgroups of kWpb worker waves with the per-XCD weighted
 // ranges (StreamPlan); else one single-wave workgroup per worker with equal
-// ranges (EvenPlan).
-template <int D, int G, bool kWeighted>
-__global__ __launch_bounds__(64 * (kWeighted ? kWpb : 1), 2) void attn_kernel(AttnArgs a) {
+// ranges (EvenPlan).  kEntries: the call may persist its step's entries.  wg:
+// the workgroup's index among the call's.
+template <int D, int G, bool kWeighted, bool kEntries>
+__device__ __forceinline__ void attn_body(const AttnArgs& a, int wg) {
   using Plan = typename std::conditional<kWeighted, WeightedPlan, EvenPlan>::type;
   constexpr int kWaves = kWeighted ? kWpb : 1;   // workers per workgroup
   const int lane = threadIdx.x & 63;
-  const int w = uni(blockIdx.x * kWaves + (int)(threadIdx.x >> 6));
+  const int w = uni(wg * kWaves + (int)(threadIdx.x >> 6));
   const int q = lane >> 4, n = lane & 15;
   const int H = a.cv.n_kv_heads;
-  // A call that persists its step's entry: Lambda's column and every
-  // sequence's entry outcome, one copy per wave (no barrier).
   constexpr int kSeq = kWeighted ? kFusedMaxBatch : 64;   // the equal-range plan takes at most 64 segments
-  __shared__ uint8_t s_tab[kWaves][128];
-  __shared__ EntryRecord s_ent[kWaves][kSeq];
-  __shared__ int4 s_cnt[kWaves][kSeq];
+  __shared__ uint8_t s_tab[kWaves][128];           // Lambda's column, a copy per wave (no barrier)
+  __shared__ EntryRecord s_ent[kSeq];
+  __shared__ int4 s_cnt[kSeq];
+  __shared__ int s_incl[kWaves > 1 ? kSeq : 1];
+  __shared__ int2 s_open[kSeq / 64], s_chunk[kSeq / 64];
   const int wv = (int)(threadIdx.x >> 6);
-  FirstCounts f;
-  if (a.tags_new) {
+  const bool fused = kEntries && a.tags_new != nullptr;
+  if (fused) {
     s_tab[wv][lane] = a.tab.a0[lane];
     s_tab[wv][64 + lane] = a.tab.amin[lane];
-    f = first_counts_entry<kSeq>(a, &s_tab[wv][0], &s_tab[wv][64], &s_ent[wv][0], &s_cnt[wv][0]);
-    if (w == 0) {                                // the merge kernel's copy
-      for (int b = lane; b < a.batch; b += 64) {
-        int4* rec = reinterpret_cast<int4*>(a.ws_seq + b * 8);
-        const EntryRecord r = s_ent[wv][b];
-        rec[0] = s_cnt[wv][b];
-        rec[1] = make_int4(r.word, r.slot, r.page, r.pos);
-      }
-    }
-  } else {
-    f = first_counts(a);
-    s_cnt[wv][lane] = make_int4(f.n_hi, f.n_win, f.n_lo, 0);
   }
-  const int n_lds = a.tags_new ? a.batch : 64;   // sequences whose counts the wave holds in LDS
-  const Plan plan = make_plan<Plan>(a, f, a.attn_blocks);
+  const CallCounts f = plan_counts<kWaves, kSeq, kEntries>(a, &s_tab[wv][0], &s_tab[wv][64], s_ent, s_cnt, s_incl,
+                                                          s_open, s_chunk);
+  if (wg == 0) {                                   // for the merge: entry outcomes, and no piece where no page is
+    for (int b = (int)threadIdx.x; b < a.batch; b += 64 * kWaves) {
+      int4* rec = reinterpret_cast<int4*>(a.ws_seq + (size_t)b * 8);
+      if (lane_len(a, f, b) == 0) rec[0] = make_int4(0, 0, 0, 0);
+      const EntryRecord r = s_ent[min(b, kSeq - 1)];
+      rec[1] = fused ? make_int4(r.word, r.slot, r.page, r.pos) : make_int4(0, 0, 0, 0);
+    }
+  }
+  int total, mx, incl;
+  call_totals<kWeighted>(a, f, total, mx, incl);
+  const Plan plan = make_plan<Plan>(a, total, mx);
   const long long start = plan.start_of(w);
   if (start >= plan.total) return;
   const long long end = plan.end_of(w);
   int b, excl;
-  locate(a, f, start, b, excl);
+  SeqPages sp;
+  locate<kWeighted>(a, f, incl, start, b, sp, excl);
   if (b < 0) return;
-  SeqPages sp = seq_pages(a, &s_cnt[wv][0], n_lds, b);
   const long long rel = start - (long long)excl * H;
   int g = (int)udiv(rel, sp.len);
   int j0 = first_page_at(sp, (int)(rel - (long long)g * sp.len));
@@ -1016,7 +1054,7 @@ __global__ __launch_bounds__(64 * (kWeighted ? kWpb : 1), 2) void attn_kernel(At
     const long long seg0 = (long long)excl * H + (long long)g * sp.len;
     if (seg0 >= end) return;
     const int j1 = end - seg0 >= sp.len ? sp.np : first_page_at(sp, (int)(end - seg0));
-    if (j0 < j1) attend_segment<D, G, Plan>(a, w, b, g, j0, j1, sp, seg0, plan, q, n, &s_ent[wv][0]);
+    if (j0 < j1) attend_segment<D, G, kEntries, Plan>(a, w, b, g, j0, j1, sp, seg0, plan, q, n, s_ent);
     if (j1 < sp.np) return;
     j0 = 0;
     if (++g == H) {                              // next sequence that holds any page
@@ -1024,10 +1062,15 @@ __global__ __launch_bounds__(64 * (kWeighted ? kWpb : 1), 2) void attn_kernel(At
       excl += sp.len;
       do {
         if (++b >= a.batch) return;
-        sp = seq_pages(a, &s_cnt[wv][0], n_lds, b);
+        sp = seq_pages(a, f, b);
       } while (sp.len == 0);
     }
   }
+}
+
+template <int D, int G, bool kWeighted>
+__global__ __launch_bounds__(64 * (kWeighted ? kWpb : 1), 2) void attn_kernel(AttnArgs a) {
+  attn_body<D, G, kWeighted, true>(a, (int)blockIdx.x);
 }
 
 // Online merge of the partials of one (sequence, KV head) by thread t of a
@@ -1085,62 +1128,46 @@ struct PieceMerge {
   }
 };
 
-// Pieces of segment (b, g) in the stream-K decomposition (sp: pages of b,
-// excl: units of the sequences before b; sp.np > 0).
-template <typename Plan>
-__device__ __forceinline__ int pieces_of(const Plan& plan, const SeqPages& sp, int excl, int g, int H) {
-  return n_pieces(plan, sp, (long long)excl * H + (long long)g * sp.len);
-}
-// Units of the sequences before b (wave-uniform).
-__device__ __forceinline__ int units_before(const AttnArgs& a, const FirstCounts& f, int b) {
-  int excl = 0;
-  for (int c0 = 0; c0 < b; c0 += 64) excl += uni(wave_sum(lane_len(a, f, c0, b)));
-  return excl;
-}
-
 // The step's entries of a call that persists them, entered into the cache
 // after the attention kernel has planned, written and attended them (one
-// wave, lane b = sequence b): counters, index lists, the block table entry
+// wave, lane l = sequence c0 + l): counters, index lists, the block table entry
 // of an opened page, the pool cursors (one page per opening entry, granted or
 // not, as the one-token append counts them) and the status flags.
-__device__ __forceinline__ void enter_entries(const AttnArgs& a) {
+__device__ __forceinline__ void enter_entries(const AttnArgs& a, int c0) {
   const CacheView& cv = a.cv;
   const int lane = threadIdx.x & 63;
-  uint32_t flags = 0u, opened_hi = 0u, opened_lo = 0u;
-  for (int c0 = 0; c0 < a.batch; c0 += 64) {
-    const int b = c0 + lane;
-    const bool live = b < a.batch;
-    const int4 r = live ? *reinterpret_cast<const int4*>(a.ws_seq + b * 8 + 4) : make_int4(0, 0, 0, 0);
-    const int word = r.x, slot = r.y, page = r.z, pos = r.w;
-    const int act = word & 3, store = act == kHigh ? kHi : kLo;
-    const bool opens = (word & kEntOpens) != 0;
-    if (live) {
-      int32_t* cnt = counters_of(cv, b, a.layer);
-      if (word & kEntCapacity) {
+  const int b = c0 + lane;
+  const bool live = b < a.batch;
+  const int4 r = live ? *reinterpret_cast<const int4*>(a.ws_seq + (size_t)b * 8 + 4) : make_int4(0, 0, 0, 0);
+  const int word = r.x, slot = r.y, page = r.z, pos = r.w;
+  const int act = word & 3, store = act == kHigh ? kHi : kLo;
+  const bool opens = (word & kEntOpens) != 0;
+  if (live) {
+    int32_t* cnt = counters_of(cv, b, a.layer);
+    if (word & kEntCapacity) {
+      cnt[kCntLost] += 1;
+    } else {
+      if (act == kDrop) {
+        cnt[kCntDrop] += 1;
+      } else if (!(word & kEntStored)) {         // no page left in its pool
         cnt[kCntLost] += 1;
       } else {
-        if (act == kDrop) {
-          cnt[kCntDrop] += 1;
-        } else if (!(word & kEntStored)) {       // no page left in its pool
-          cnt[kCntLost] += 1;
-        } else {
-          if (opens) block_table_of(cv, b, a.layer, store)[slot / kPage] = page;
-          index_list_of(cv, b, a.layer, store)[slot] = pos;
-          cnt[store] = slot + 1;
-          if (word & kEntForced) cnt[kCntForced] += 1;
-        }
-        cnt[kCntPos] = pos + 1;
+        if (opens) block_table_of(cv, b, a.layer, store)[slot / kPage] = page;
+        index_list_of(cv, b, a.layer, store)[slot] = pos;
+        cnt[store] = slot + 1;
+        if (word & kEntForced) cnt[kCntForced] += 1;
       }
-      flags |= (uint32_t)word >> 8;
+      cnt[kCntPos] = pos + 1;
     }
-    opened_hi += (uint32_t)__popcll(__ballot(live && opens && store == kHi));
-    opened_lo += (uint32_t)__popcll(__ballot(live && opens && store == kLo));
   }
+  const int opened_hi = __popcll(__ballot(live && opens && store == kHi));
+  const int opened_lo = __popcll(__ballot(live && opens && store == kLo));
+  uint32_t flags = live ? (uint32_t)word >> 8 : 0u;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) flags |= (uint32_t)__shfl_xor((int)flags, off);
   if (lane == 0) {
-    if (opened_hi) atomicAdd(&cv.status[2], opened_hi);
-    if (opened_lo) atomicAdd(&cv.status[3], opened_lo);
+    if (opened_hi) atomicAdd(&cv.status[2], (uint32_t)opened_hi);
+    if (opened_lo) atomicAdd(&cv.status[3], (uint32_t)opened_lo);
     if (flags) atomicOr(cv.status, flags);
   }
 }
@@ -1157,8 +1184,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {   // merg
   __shared__ __align__(16) uint16_t s_out[G][D];
   const int t = threadIdx.x;
   const int H = a.cv.n_kv_heads;
-  if (a.tags_new && blockIdx.x == gridDim.x - 1) {   // the extra block: the step's entries
-    if (t < 64) enter_entries(a);
+  const int segs = a.batch * H;
+  if ((int)blockIdx.x >= segs) {                   // the extra blocks: the step's entries, 64 sequences each
+    if (t < 64) enter_entries(a, ((int)blockIdx.x - segs) * 64);
     return;
   }
   const int b = uni(blockIdx.x / H), g = uni(blockIdx.x % H);
@@ -1166,19 +1194,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {   // merg
   const size_t blk0 = ((size_t)b * H + g) * a.splits;
   const int q = t / (NM * 16), k = (t / 16) % NM, n = t % 16;
   PieceMerge<D, G> pm;
-  // The first pieces are loaded before the piece count is known (slots
-  // below `splits` are in bounds; those past the count are skipped), so their
-  // latency overlaps that of the counters the count comes from.
+  // The first pieces are loaded with the piece count (slots below `splits`
+  // are in bounds; those past the count are skipped), so the latencies overlap.
   pm.load(a, blk0, t, q, 0, a.splits - 1);
-  const FirstCounts f = planned_counts(a);
-  const SeqPages sp = seq_pages(a, f, b);
-  if (sp.np == 0) {
+  const int nparts = pieces_of(a, b, g);
+  if (nparts == 0) {
     for (int i = t; i < G * D; i += merge_threads<D, G>()) a.out[row0 * D + i] = 0;
     if (a.lse && t < G) a.lse[row0 + t] = -INFINITY;
     return;
   }
-  const WeightedPlan plan = stream_plan(a, f, a.attn_blocks);
-  const int nparts = pieces_of(plan, sp, units_before(a, f, b), g, H);
   pm.init();
   for (int p0 = 0; p0 < nparts; p0 += PieceMerge<D, G>::kBatch) {
     if (p0 > 0) pm.load(a, blk0, t, q, p0, nparts - 1);
@@ -1211,11 +1235,11 @@ __global__ __launch_bounds__(64) void attn_merge_sliced_kernel(AttnArgs a) {
   constexpr int NM = D / 16, X = merge_threads<D, G>() / 16;
   const int lane = threadIdx.x, j = lane >> 4, n = lane & 15;
   const int H = a.cv.n_kv_heads;
-  if (a.tags_new && blockIdx.x == gridDim.x - 1) {   // the extra block: the step's entries
-    enter_entries(a);
+  const int seg = uni(blockIdx.x / X), x = uni(blockIdx.x % X);
+  if (seg >= a.batch * H) {                        // the extra block: the step's entries (at most 64 sequences)
+    enter_entries(a, 0);
     return;
   }
-  const int seg = uni(blockIdx.x / X), x = uni(blockIdx.x % X);
   const int b = seg / H, g = seg % H;
   const int q = x / NM, k = x % NM, t = 16 * x + n;
   const size_t row0 = (size_t)b * a.n_q_heads + (size_t)g * G;
@@ -1226,17 +1250,14 @@ __global__ __launch_bounds__(64) void attn_merge_sliced_kernel(AttnArgs a) {
   // (the ranges' 1/PASK_SMALL_PIECES floor), not the workspace's last, so the
   // loads past the count re-read one slot instead of stale partials.
   pm.load(a, blk0, t, q, j, min(a.splits, PASK_SMALL_PIECES + 1) - 1, 4);
-  const FirstCounts f = planned_counts(a);
-  const SeqPages sp = seq_pages(a, f, b);
-  if (sp.np == 0) {
+  const int nparts = pieces_of(a, b, g);
+  if (nparts == 0) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (j == 0 && 4 * q + r < G) a.out[(row0 + 4 * q + r) * D + 16 * k + n] = 0;
     if (a.lse && j == 0 && k == 0 && n < 4 && 4 * q + n < G) a.lse[row0 + 4 * q + n] = -INFINITY;
     return;
   }
-  const EvenPlan plan = even_plan(a, f, a.attn_blocks);
-  const int nparts = pieces_of(plan, sp, units_before(a, f, b), g, H);
   pm.init();
   for (int p0 = 0; p0 < nparts; p0 += 4 * kB) {
     const int first = p0 + j;
@@ -1273,32 +1294,22 @@ __global__ __launch_bounds__(64) void attn_merge_sliced_kernel(AttnArgs a) {
 // attention-output distortion (Eq. 4)
 // ---------------------------------------------------------------------------
 
-// Normalised fp32 outputs of heads 4q..4q+3 at thread t's dim for (b, g) in
-// the reference (or_) and the intervened (oi) cache: both sets of partials
-// loaded before either is merged, so their latencies overlap; 0 for an
-// empty history.
+// The attention of the distortion's two caches as one launch, half of the
+// workgroups (hence of the workers) each: two launches in turn each paid the
+// launch, the plan and a tail of their own (16 sequences, prompts of
+// 1,024-4,096 tokens, 8 KV heads, D 128: 2 x 37.3 us; one launch 67.2 us).
 template <int D, int G>
-__device__ __forceinline__ void merged_pair(const AttnArgs& ref, const WeightedPlan& pr, const SeqPages& sr, int er,
-                                            const AttnArgs& itv, const WeightedPlan& pi, const SeqPages& si, int ei,
-                                            int b, int g, int t, int q, float (&or_)[4], float (&oi)[4]) {
-  constexpr int kB = 4;                          // pieces per batch and cache: both in flight, no spills
-  const int H = ref.cv.n_kv_heads;
-  const int nr = sr.np ? pieces_of(pr, sr, er, g, H) : 0, ni = si.np ? pieces_of(pi, si, ei, g, H) : 0;
-  const size_t blk0 = ((size_t)b * H + g);
-  PieceMerge<D, G, kB> mr, mi;
-  mr.init();
-  mi.init();
-  for (int p0 = 0; p0 < max(nr, ni); p0 += kB) {
-    if (p0 < nr) mr.load(ref, blk0 * ref.splits, t, q, p0, nr - 1);
-    if (p0 < ni) mi.load(itv, blk0 * itv.splits, t, q, p0, ni - 1);
-    if (p0 < nr) mr.fold(nr - p0);
-    if (p0 < ni) mi.fold(ni - p0);
+__global__ __launch_bounds__(64 * kWpb, 2) void attn_pair_kernel(AttnArgs ref, AttnArgs itv) {
+  const int half = (int)gridDim.x / 2;
+  const bool second = (int)blockIdx.x >= half;
+  AttnArgs a = ref;
+  if (second) {                                    // what differs between the two
+    a.cv = itv.cv;
+    a.ws_o = itv.ws_o;
+    a.ws_ml = itv.ws_ml;
+    a.ws_seq = itv.ws_seq;
   }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    or_[r] = nr ? mr.acc[r] / mr.L[r] : 0.0f;
-    oi[r] = ni ? mi.acc[r] / mi.L[r] : 0.0f;
-  }
+  attn_body<D, G, true, false>(a, (int)blockIdx.x - (second ? half : 0));
 }
 
 __device__ __forceinline__ float wave_sum_f(float x) {
@@ -1307,56 +1318,63 @@ __device__ __forceinline__ float wave_sum_f(float x) {
   return x;
 }
 
-// KV heads a distortion block handles at once: that many merge groups of
-// merge_threads threads, at most 512 threads (256 VGPRs per thread).
+// One block per (sequence b, KV head g): the outputs of its G query heads over
+// the reference cache (partials of `ref`) and the intervened one (`itv`) in
+// fp32, both sets of partials loaded before either is merged, the squared L2
+// distance of each head's rows summed over the D dims, and the largest of the
+// G left in the segment's first partial.  The block that arrives last of the
+// sequence's (a counter the attention has zeroed) adds the maximum over all
+// query heads (Eq. 4, inside the expectation) to dist[b].  Nothing is done for
+// a sequence with in_s[b] == 0 (in_s null: every sequence counts).  One block
+// per sequence, eight KV heads at a time, left all but B compute units idle:
+// 50.4 us at 16 sequences of up to 4,608 entries, 13.6 us so.
 template <int D, int G>
-constexpr int distortion_heads() { return 512 / merge_threads<D, G>() < 8 ? 512 / merge_threads<D, G>() : 8; }
-
-// One block per sequence b: for every KV head g (distortion_heads of them at
-// a time, one merge group each), the outputs of its G query heads over the
-// reference cache (partials of `ref`) and the intervened one (`itv`) in fp32,
-// the squared L2 distance of each head's rows summed over the D dims, and the
-// maximum over all query heads (Eq. 4, inside the expectation), added to
-// dist[b] when in_s is null or in_s[b] != 0.
-template <int D, int G>
-__global__ __launch_bounds__(512) void distortion_kernel(AttnArgs ref, AttnArgs itv, const uint8_t* in_s,
-                                                          float* dist) {
-  constexpr int NM = D / 16;
-  constexpr int G4 = G > 4 ? G : 4;
-  constexpr int MT = merge_threads<D, G>();
-  constexpr int GP = distortion_heads<D, G>();
-  __shared__ float s_d2[GP][G4];
-  const int b = uni(blockIdx.x);
-  if (in_s && in_s[b] == 0) return;
-  const int gl = threadIdx.x / MT, t = threadIdx.x % MT;   // merge group, thread in it
+__global__ __launch_bounds__(256) void distortion_kernel(AttnArgs ref, AttnArgs itv, const uint8_t* in_s,
+                                                         float* dist) {
+  constexpr int NM = D / 16, G4 = G > 4 ? G : 4, MT = merge_threads<D, G>(), kB = 8;
+  __shared__ float s_d2[MT / 64][4];
   const int H = ref.cv.n_kv_heads;
-  const int q = t / (NM * 16);
-  const FirstCounts fr = first_counts(ref), fi = first_counts(itv);
-  const WeightedPlan pr = stream_plan(ref, fr, ref.attn_blocks), pi = stream_plan(itv, fi, itv.attn_blocks);
-  const SeqPages sr = seq_pages(ref, fr, b), si = seq_pages(itv, fi, b);
-  const int er = units_before(ref, fr, b), ei = units_before(itv, fi, b);
-  float worst = 0.0f;
-  for (int g0 = 0; g0 < H; g0 += GP) {
-    if (threadIdx.x < GP * G4) s_d2[threadIdx.x / G4][threadIdx.x % G4] = 0.0f;
-    __syncthreads();
-    const int g = g0 + gl;
-    if (g < H) {                                 // whole merge groups (waves) take this branch alike
-      float o_r[4], o_i[4];
-      merged_pair<D, G>(ref, pr, sr, er, itv, pi, si, ei, b, g, t, q, o_r, o_i);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {              // each wave holds 64 dims of heads 4q..4q+3
-        const float e = o_r[r] - o_i[r];
-        const float w = wave_sum_f(e * e);
-        if ((t & 63) == 0) atomicAdd(&s_d2[gl][4 * q + r], w);
-      }
+  const int b = uni(blockIdx.x / H), g = uni(blockIdx.x % H);
+  if (in_s && in_s[b] == 0) return;
+  const int t = threadIdx.x, q = t / (NM * 16);
+  const size_t seg = (size_t)b * H + g;
+  PieceMerge<D, G, kB> mr, mi;
+  mr.load(ref, seg * ref.splits, t, q, 0, ref.splits - 1);
+  mi.load(itv, seg * itv.splits, t, q, 0, itv.splits - 1);
+  const int nr = pieces_of(ref, b, g), ni = pieces_of(itv, b, g);
+  mr.init();
+  mi.init();
+  for (int p0 = 0; p0 < max(nr, ni); p0 += kB) {
+    if (p0 > 0) {
+      mr.load(ref, seg * ref.splits, t, q, p0, max(nr, 1) - 1);
+      mi.load(itv, seg * itv.splits, t, q, p0, max(ni, 1) - 1);
     }
-    __syncthreads();
-    if (threadIdx.x == 0)
-      for (int j = 0; j < GP && g0 + j < H; ++j)
-        for (int h = 0; h < G; ++h) worst = fmaxf(worst, s_d2[j][h]);
-    __syncthreads();
+    mr.fold(nr - p0);
+    mi.fold(ni - p0);
   }
-  if (threadIdx.x == 0) dist[b] += worst;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {                    // each wave holds 64 dims of heads 4q..4q+3
+    const float e = (nr ? mr.acc[r] / mr.L[r] : 0.0f) - (ni ? mi.acc[r] / mi.L[r] : 0.0f);
+    const float d2 = wave_sum_f(e * e);
+    if ((t & 63) == 0) s_d2[t / 64][r] = d2;
+  }
+  __syncthreads();                                 // also: every thread has read the partials
+  if (t != 0) return;
+  constexpr int kWq = D / 64 > 0 ? NM * 16 / 64 : 1;   // waves per head quad
+  float worst = 0.0f;
+  for (int h = 0; h < G; ++h) {
+    float d2 = 0.0f;
+    for (int i = 0; i < kWq; ++i) d2 += s_d2[h / 4 * kWq + i][h % 4];
+    worst = fmaxf(worst, d2);
+  }
+  float* slot = ref.ws_ml + seg * ref.splits * (G4 * 2);
+  __hip_atomic_store(slot, worst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int* arrived = itv.ws_seq + (size_t)b * 8 + 4;
+  if (__hip_atomic_fetch_add(arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != H - 1) return;
+  for (int o = 0; o < H; ++o)
+    worst = fmaxf(worst, __hip_atomic_load(ref.ws_ml + ((size_t)b * H + o) * ref.splits * (G4 * 2), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT));
+  dist[b] += worst;
 }
 
 }  // namespace
@@ -1416,7 +1434,7 @@ hipError_t launch_attention(const AttnArgs& args, int group_size, hipStream_t s)
   const int segs = a.batch * a.cv.n_kv_heads;
   const bool small = segs <= kSmallSegments;
   if (a.tags_new && (a.batch > kFusedMaxBatch || a.cv.window != 0 || a.ws_seq == nullptr)) return hipErrorInvalidValue;
-  const int extra = a.tags_new ? 1 : 0;           // the merge block that enters the step's entries
+  const int extra = a.tags_new ? (a.batch + 63) / 64 : 0;   // merge blocks that enter the step's entries
 #define PASK_CASE(DD, GG)                                                        \
   if (D == DD && group_size == GG) {                                             \
     a.attn_blocks = small ? attn_grid<DD, GG, false>() : attn_grid<DD, GG, true>(); \
@@ -1444,13 +1462,12 @@ hipError_t launch_distortion(const AttnArgs& ref_args, const AttnArgs& itv_args,
   const dim3 block(64 * kWpb);
 #define PASK_CASE(DD, GG)                                                        \
   if (D == DD && group_size == GG) {                                             \
-    ref.attn_blocks = itv.attn_blocks = attn_grid<DD, GG, true>();               \
+    ref.attn_blocks = itv.attn_blocks = attn_grid<DD, GG, true>() / (2 * kWpb) * kWpb; /* half the workers each */ \
     ref.tags_new = itv.tags_new = nullptr;                                       \
     ref.min_pages = itv.min_pages = kMinPagesPerBlock;                           \
     if (ref.attn_blocks <= 0) return hipErrorInvalidDeviceFunction;              \
-    attn_kernel<DD, GG, true><<<dim3(ref.attn_blocks / kWpb), block, 0, s>>>(ref); \
-    attn_kernel<DD, GG, true><<<dim3(itv.attn_blocks / kWpb), block, 0, s>>>(itv); \
-    distortion_kernel<DD, GG><<<dim3(ref.batch), dim3(merge_threads<DD, GG>() * distortion_heads<DD, GG>()), 0, s>>>(ref, itv, in_s, dist); \
+    attn_pair_kernel<DD, GG><<<dim3(2 * (ref.attn_blocks / kWpb)), block, 0, s>>>(ref, itv); \
+    distortion_kernel<DD, GG><<<dim3(ref.batch * ref.cv.n_kv_heads), dim3(merge_threads<DD, GG>()), 0, s>>>(ref, itv, in_s, dist); \
     return hipGetLastError();                                                    \
   }
   PASK_CASE(64, 1) PASK_CASE(64, 2) PASK_CASE(64, 4) PASK_CASE(64, 8)

@@ -76,7 +76,7 @@ struct CacheView {
   int32_t* counters;      // [max_batch][n_layers][8]
   int32_t* block_table;   // [max_batch][n_layers][2][max_pages]
   int32_t* index_list;    // [max_batch][n_layers][2][max_tokens]
-  int32_t* staging;       // [max_batch][staging_stride]
+  int32_t* staging;       // [max_batch][staging_stride]: a bulk append's scratch (the last four words)
   BudgetTable* budget;
   uint8_t* ring_act;      // [max_batch][n_layers][window]: action | forced << 2
   uint8_t* hi_pool;       // recent-window pages first, then the HIGH store
@@ -127,7 +127,7 @@ struct AttnArgs {
   const uint8_t* tags_new;  // [batch]
   const uint16_t* k_new;    // bf16 bits [batch][Hkv][D]
   const uint16_t* v_new;
-  int32_t* ws_seq;          // [batch][8]: the merge's page counts and the entry's outcome
+  int32_t* ws_seq;          // [batch][8]: 8 u16 piece counts (one per KV head), then the entry's outcome
   TableColumn tab;          // Lambda's column of the layer (with tags_new)
   float scale_log2;         // softmax_scale * log2(e)
   int32_t layer, batch, n_q_heads, splits;   // splits: partials per (b, g) the workspace holds
@@ -141,10 +141,11 @@ struct AttnArgs {
 // several thread groups at once.
 constexpr int kSmallSegments = 64;
 constexpr int kSmallPartials = 4096;
-// Calls that persist their step's entry themselves: every worker decides the
-// entries of all sequences, 64 at a time (one per lane of its wave), and
-// keeps their counts and outcomes in LDS.
-constexpr int kFusedMaxBatch = 256;
+// Calls that persist their step's entry themselves: every workgroup decides
+// the entries of all sequences, 64 at a time (one per lane of a wave), and
+// keeps their counts and outcomes in LDS (32 bytes per sequence, two
+// workgroups per compute unit).
+constexpr int kFusedMaxBatch = 1024;
 
 // The library-owned scratch of pask_decode_attn_noalloc: a device array of
 // kScratchBytes in pask_attn.hip, one copy per GPU.  scratch_workspace gives

@@ -143,12 +143,12 @@ struct EvenPlan {
     const long long e = (long long)(w + 1) * U;
     return e < total ? e : total;
   }
-  __host__ __device__ __forceinline__ long long block_of(long long u) const { return u / U; }
+  __host__ __device__ __forceinline__ long long block_of(long long u) const { return udiv(u, U); }
 };
 __host__ __device__ __forceinline__ EvenPlan even_plan_of(long long total, int mx, int splits, int min_pages, int n) {
   EvenPlan p;
   p.total = total;
-  const long long even = (total + n - 1) / n;
+  const long long even = udiv(total + n - 1, n);
   int U = kUnit * min_pages;
   if (even > U) U = (int)(even < 0x7FFFFFFF ? even : 0x7FFFFFFF);
   const int lo1 = cdiv(mx, splits - 1);

@@ -1,5 +1,5 @@
-"""The bulk append's plan at the sizes where it splits differently: around one
-token per lane and round, around a whole chunk of tokens and across chunks,
+"""The bulk append's plan, and the plan of a decode call of many sequences, at
+the sizes where they split differently: around one token per lane and round, around a whole chunk of tokens and across chunks,
 with a recent window, with a pool that runs out inside a chunk, and with the
 online controller near its reserves.  Decisions, slots, counters, lists and
 budgets against the CPU oracle, all exact."""
@@ -9,8 +9,9 @@ import pytest
 import torch
 
 import oracle
-from tests.gpu_util import budgets, say
+from tests.gpu_util import Scenario, budgets, say
 from workload import make_policy
+from workload.tags import function_call_tags
 from workload.policy import PolicyTable, contiguous_groups, pack_blob
 
 pytestmark = pytest.mark.gpu
@@ -141,3 +142,21 @@ def test_controller_near_its_reserves(n, seed):
         for layer in range(L):
             _check_lists(sess, b, layer, acts[:, gol[layer]], (n, seed, b, layer))
     assert len(kinds) >= 3, kinds
+
+
+@pytest.mark.parametrize("B", [65, 320, 1024, 1025])
+def test_decode_call_of_many_sequences(B):
+    """A decode call that persists its tokens plans 64 sequences per wave and
+    pass, up to 1,024 of them; above, the one-token append comes first and the
+    plan reads the counters past the 1,024th.  Short ragged prompts, some
+    empty, so that pages open in every chunk; two steps, all compared."""
+    say(f"case: decode plan of {B} sequences")
+    pol = make_policy(6, 1, 1, 0.4, seed=B)
+    P = [(7 * b) % 35 for b in range(B)]
+    base = function_call_tags(B + 2, 5)
+    tags = np.stack([base[b:b + 2] for b in range(B)])
+    sc = Scenario(pol, B=B, L=1, Hq=2, Hkv=1, D=64, prompt_lens=P, gen_tags=tags, seed=B)
+    sc.fill_prompt()
+    for t in range(2):
+        sc.decode_step(t)
+    sc.check_state()
