@@ -12,9 +12,8 @@
 //                registers.
 //   attn_merge   per (sequence, KV head): combine the partials of its pieces
 //                (max, sum, values) into bf16 outputs; zero for empty histories.
-//                Calls with few (sequence, KV head) segments cut them into
-//                pieces of at least 4 pages and 1/32 of the longest segment
-//                and spread each segment's merge over several single-wave
+//                Calls with few (sequence, KV head) segments cut each of them
+//                by itself and spread its merge over several single-wave
 //                blocks (attn_merge_sliced).
 //   distortion   the attention-output distortion of Eq. 4: the partials of a
 //                reference and an intervened cache merged in fp32, the squared
@@ -39,17 +38,12 @@ namespace {
 //
 // Stream-K: the work is the list of (sequence b, KV head g, page) triples,
 // HIGH and window pages of a (b, g) before its LOW pages, each page weighing
-// 32 units.  The grid holds one worker wave per resident wave slot of the
-// chip, and worker w takes the w-th of contiguous unit ranges, so every
-// worker starts at launch.  Calls with more than 64 (b, g) segments run four
-// workers per workgroup, and the workers of workgroups on the odd-numbered
-// XCDs (odd workgroup index: workgroups are dealt to the 8 XCDs in turn)
-// take PASK_ODD_WEIGHT/16 of an even one's range: their waves stream pages
-// about 10% slower, so with equal ranges the even XCDs idle through the last
-// ~15 us of the call.  Calls with at most 64 segments run single-wave
-// workgroups with equal ranges.  A range crossing a (b, g) boundary closes
-// that segment with a partial block; every range is at least what keeps every
-// (b, g) within as many pieces as the workspace holds partials.
+// 32 units.  Calls with more than kAlignedSegments (b, g) segments: worker w of
+// stream_workers takes the w-th of equal contiguous unit ranges; a range
+// crossing a (b, g) boundary closes that segment with a partial block, and
+// every range is at least what keeps every (b, g) within as many pieces as the
+// workspace holds partials.  Calls with fewer segments: single-wave
+// workgroups, one piece of one segment each (small_units).
 //
 // Per page (16 slots x all G query heads of KV head g), one wave:
 //   scores  S^T = K Q^T on v_mfma_f32_16x16x32_bf16: rows = slots, columns
@@ -429,15 +423,15 @@ __device__ __forceinline__ int window_slots(const AttnArgs& a, int n_pos) { retu
 // in LDS, as (n_hi, n_win, n_lo, n_x), n_x = 1 when the call persists and
 // attends an entry of the sequence; those of further sequences (only in calls
 // that persist nothing) are read from the counters.  incl: the units of each
-// sequence and the lower ones of its chunk of 64; chunk: each chunk's units
-// and its longest sequence's.  A workgroup of one wave keeps its only chunk's
+// sequence and the lower ones of its chunk of 64; chunk: each chunk's units,
+// its longest sequence's and its units of LOW pages.  A workgroup of one wave keeps its only chunk's
 // in registers instead (lane = sequence).
 struct CallCounts {
   const int4* lds;
   int n_lds;
   const int* incl;
-  const int2* chunk;
-  int lane_incl, lane_len;
+  const int4* chunk;
+  int lane_incl, lane_len, lane_lo, lane_x;        // stored pages only; lane_lo: units of LOW pages; lane_x: n_x
 };
 
 // ---------------------------------------------------------------------------
@@ -468,7 +462,7 @@ constexpr int kEntStored = 4, kEntForced = 8, kEntOpens = 16, kEntCapacity = 32;
 template <int kWaves, int kSeq, bool kEntries>     // sequences s_cnt and s_ent hold; the call may persist entries
 __device__ __forceinline__ CallCounts plan_counts(const AttnArgs& a, const uint8_t* s_a0, const uint8_t* s_amin,
                                                   EntryRecord* s_ent, int4* s_cnt, int* s_incl, int2* s_open,
-                                                  int2* s_chunk) {
+                                                  int4* s_chunk) {
   constexpr int kC = kSeq / 64 / kWaves;           // chunks of one wave
   static_assert(kC * 64 * kWaves == kSeq, "whole chunks");
   const CacheView& cv = a.cv;
@@ -488,17 +482,19 @@ __device__ __forceinline__ CallCounts plan_counts(const AttnArgs& a, const uint8
       if (fused) tag[i] = (int)a.tags_new[b];
     }
   }
-  CallCounts f{s_cnt, n_lds, s_incl, s_chunk, 0, 0};
+  CallCounts f{s_cnt, n_lds, s_incl, s_chunk, 0, 0, 0, 0};
   auto counted = [&](int chunk, const int4& c) {   // the counts of sequence 64 chunk + lane (0 past the batch)
-    const int len = len_of(c.x, c.y, c.z, c.w), incl = wave_inclusive_scan(len);
+    const int len = len_of(c.x, c.y, c.z, kWaves == 1 ? 0 : c.w), incl = wave_inclusive_scan(len);
     s_cnt[chunk * 64 + lane] = c;
     if constexpr (kWaves == 1) {
       f.lane_incl = incl;
       f.lane_len = len;
+      f.lane_lo = low_len_of(c.z);
+      f.lane_x = c.w;
     } else {
       s_incl[chunk * 64 + lane] = incl;
-      const int longest = wave_max(len);
-      if (lane == 63) s_chunk[chunk] = make_int2(incl, longest);
+      const int longest = wave_max(len), low = wave_inclusive_scan(low_len_of(c.z));
+      if (lane == 63) s_chunk[chunk] = make_int4(incl, longest, low, 0);
     }
   };
   if (!fused) {
@@ -607,49 +603,34 @@ __device__ __forceinline__ int lane_len(const AttnArgs& a, const CallCounts& f, 
 constexpr int kWpb = PASK_ATTN_WPB;   // workers (waves) per workgroup of the weighted attention kernel
 using WeightedPlan = StreamPlan<kWpb>;
 constexpr int kMinPagesPerBlock = kUnitTokens / kPage;   // 8 pages: the workspace's piece size
-// Calls with few segments: workers of at least 4 pages (8 and 12 measured
-// slower at one Qwen3-4B-shaped sequence of 2.3k entries, 2 slower too), and
-// of at least 1/PASK_SMALL_PIECES of the longest segment.
+// Calls with few segments: pieces of at least 4 pages (8 and 12 measured slower
+// at one Qwen3-4B-shaped sequence of 2.3k entries, 2 slower too).
 constexpr int kSmallMinPages = 4;
-static_assert(PASK_SMALL_PIECES >= 1, "pieces per segment");
 static_assert(PASK_ODD_WEIGHT >= 1 && PASK_ODD_WEIGHT <= 16, "odd-XCD worker weight out of range");
 
-// The units of the whole call (one KV head), its longest sequence's, and the
-// units of chunk `lane` and the lower ones (a workgroup of one wave: of
-// sequence `lane` and the lower ones).
-template <bool kWeighted>
-__device__ __forceinline__ void call_totals(const AttnArgs& a, const CallCounts& f, int& total, int& mx, int& incl) {
+// The units of the whole call (one KV head), those of LOW pages among them, its
+// longest sequence's units, and the units of chunk `lane` and the lower ones.
+__device__ __forceinline__ void call_totals(const AttnArgs& a, const CallCounts& f, int& total, int& total_lo, int& mx,
+                                            int& incl) {
   const int lane = threadIdx.x & 63;
-  if constexpr (!kWeighted) {
-    incl = f.lane_incl;
-    total = __builtin_amdgcn_readlane(incl, 63);
-    mx = wave_max(f.lane_len);
-  } else {
-    const int2 c = lane < (f.n_lds + 63) / 64 ? f.chunk[lane] : make_int2(0, 0);
-    incl = wave_inclusive_scan(c.x);
-    total = __builtin_amdgcn_readlane(incl, 63);
-    mx = wave_max(c.y);
-    for (int c0 = f.n_lds; c0 < a.batch; c0 += 64) {   // n_lds is a multiple of 64 here
-      const int len = lane_len(a, f, c0 + lane);
-      total += __builtin_amdgcn_readlane(wave_inclusive_scan(len), 63);
-      mx = max(mx, wave_max(len));
-    }
+  const int4 c = lane < (f.n_lds + 63) / 64 ? f.chunk[lane] : make_int4(0, 0, 0, 0);
+  incl = wave_inclusive_scan(c.x);
+  total = __builtin_amdgcn_readlane(incl, 63);
+  total_lo = __builtin_amdgcn_readlane(wave_inclusive_scan(c.z), 63);
+  mx = wave_max(c.y);
+  for (int c0 = f.n_lds; c0 < a.batch; c0 += 64) {   // n_lds is a multiple of 64 here
+    const int len = lane_len(a, f, c0 + lane);
+    const int lo = c0 + lane < a.batch ? low_len_of(counters_of(a.cv, c0 + lane, a.layer)[kCntLo]) : 0;
+    total += __builtin_amdgcn_readlane(wave_inclusive_scan(len), 63);
+    total_lo += __builtin_amdgcn_readlane(wave_inclusive_scan(lo), 63);
+    mx = max(mx, wave_max(len));
   }
-}
-template <typename Plan>
-__device__ __forceinline__ Plan make_plan(const AttnArgs& a, int total, int mx) {
-  const long long units = (long long)total * a.cv.n_kv_heads;
-  if constexpr (std::is_same<Plan, EvenPlan>::value)
-    return even_plan_of(units, mx, min(a.splits, PASK_SMALL_PIECES + 1), a.min_pages, a.attn_blocks);
-  else
-    return stream_plan_of<kWpb>(units, mx, a.splits, a.min_pages, a.attn_blocks, PASK_ODD_WEIGHT);
 }
 
 // Sequence whose segments hold unit P < the call's units (incl: call_totals'),
 // its pages, and the units of the sequences before it.  A sequence without a
 // page adds nothing to the running sums, so the first sum past P is the
 // sequence's own.
-template <bool kWeighted>
 __device__ __forceinline__ void locate(const AttnArgs& a, const CallCounts& f, int incl, long long P, int& b_out,
                                        SeqPages& sp, int& excl_out) {
   const long long H = a.cv.n_kv_heads;
@@ -663,19 +644,15 @@ __device__ __forceinline__ void locate(const AttnArgs& a, const CallCounts& f, i
     upto = __builtin_amdgcn_readlane(sum, src);
     return true;
   };
-  if constexpr (!kWeighted) {
-    first_past(incl, 0);
+  if (first_past(incl, 0)) {                       // the chunk
+    const int c = b, base = c > 0 ? __builtin_amdgcn_readlane(incl, c - 1) : 0;
+    first_past(f.incl[c * 64 + lane] + base, c * 64);
   } else {
-    if (first_past(incl, 0)) {                     // the chunk
-      const int c = b, base = c > 0 ? __builtin_amdgcn_readlane(incl, c - 1) : 0;
-      first_past(f.incl[c * 64 + lane] + base, c * 64);
-    } else {
-      int base = __builtin_amdgcn_readlane(incl, 63);
-      for (int c0 = f.n_lds; c0 < a.batch; c0 += 64) {
-        const int sum = wave_inclusive_scan(lane_len(a, f, c0 + lane)) + base;
-        if (first_past(sum, c0)) break;
-        base = __builtin_amdgcn_readlane(sum, 63);
-      }
+    int base = __builtin_amdgcn_readlane(incl, 63);
+    for (int c0 = f.n_lds; c0 < a.batch; c0 += 64) {
+      const int sum = wave_inclusive_scan(lane_len(a, f, c0 + lane)) + base;
+      if (first_past(sum, c0)) break;
+      base = __builtin_amdgcn_readlane(sum, 63);
     }
   }
   b_out = b;
@@ -920,12 +897,11 @@ __device__ __forceinline__ uint16_t& pieces_of(const AttnArgs& a, int b, int g) 
   return reinterpret_cast<uint16_t*>(a.ws_seq + (size_t)b * 8)[g];
 }
 
-// Pages [j0, j1) of (b, g) (HIGH store, recent window, LOW store): this
-// piece's partial of (b, g), combined with the others by attn_merge.
-template <int D, int G, bool kEntries, typename Plan>
-__device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, int g, int j0, int j1, const SeqPages& sp,
-                                               long long seg0, const Plan& plan, int q, int n,
-                                               const EntryRecord* ent) {
+// Pages [j0, j1) of (b, g) (HIGH store, recent window, LOW store), piece
+// `slot` of the segment: its partial of (b, g), combined with the others by attn_merge.
+template <int D, int G, bool kEntries>
+__device__ __forceinline__ void attend_segment(const AttnArgs& a, int slot, int b, int g, int j0, int j1,
+                                               const SeqPages& sp, int q, int n, const EntryRecord* ent) {
   using PL = PageLayout<D>;
   const CacheView& cv = a.cv;
   const int H = cv.n_kv_heads;
@@ -985,10 +961,9 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, 
   // Rows past G hold finite values that are never read into an output.
   constexpr int G4 = G > 4 ? G : 4;
   const float l_n = head_sum(st.l);              // head n, over all slots
-  const int slot = (int)(w - plan.block_of(seg0));   // < a.splits by the choice of range sizes
   if (j1 == sp.np && (threadIdx.x & 63) == 0)       // the segment's last piece: their number, for the merge
     pieces_of(a, b, g) = (uint16_t)max(1, min(slot + 1, a.splits));
-  if (slot < 0 || slot >= a.splits) {            // never expected: report it, write nothing
+  if (slot < 0 || slot >= a.splits) {            // never expected (the choice of range sizes): report it, write nothing
     if ((threadIdx.x & 63) == 0) atomicOr(a.cv.status, (uint32_t)PASK_FLAG_WORKSPACE);
     return;
   }
@@ -1003,24 +978,23 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int w, int b, 
   if (q == 0 && n < G4) *reinterpret_cast<float2*>(a.ws_ml + (blk * G4 + n) * 2) = make_float2(st.m, l_n);
 }
 
-// kWeighted: workgroups of kWpb worker waves with the per-XCD weighted
-// ranges (StreamPlan); else one single-wave workgroup per worker with equal
-// ranges (EvenPlan).  kEntries: the call may persist its step's entries.  wg:
+// kWeighted: workgroups of kWpb worker waves, ranges over the whole list
+// (StreamPlan); else one single-wave workgroup per piece of a segment
+// (small_piece).  kEntries: the call may persist its step's entries.  wg:
 // the workgroup's index among the call's.
 template <int D, int G, bool kWeighted, bool kEntries>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, int wg) {
-  using Plan = typename std::conditional<kWeighted, WeightedPlan, EvenPlan>::type;
   constexpr int kWaves = kWeighted ? kWpb : 1;   // workers per workgroup
   const int lane = threadIdx.x & 63;
-  const int w = uni(wg * kWaves + (int)(threadIdx.x >> 6));
   const int q = lane >> 4, n = lane & 15;
   const int H = a.cv.n_kv_heads;
-  constexpr int kSeq = kWeighted ? kFusedMaxBatch : 64;   // the equal-range plan takes at most 64 segments
+  constexpr int kSeq = kWeighted ? kFusedMaxBatch : 64;   // calls with few segments hold at most 64 sequences
   __shared__ uint8_t s_tab[kWaves][128];           // Lambda's column, a copy per wave (no barrier)
   __shared__ EntryRecord s_ent[kSeq];
   __shared__ int4 s_cnt[kSeq];
   __shared__ int s_incl[kWaves > 1 ? kSeq : 1];
-  __shared__ int2 s_open[kSeq / 64], s_chunk[kSeq / 64];
+  __shared__ int2 s_open[kSeq / 64];
+  __shared__ int4 s_chunk[kSeq / 64];
   const int wv = (int)(threadIdx.x >> 6);
   const bool fused = kEntries && a.tags_new != nullptr;
   if (fused) {
@@ -1037,33 +1011,58 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int wg) {
       rec[1] = fused ? make_int4(r.word, r.slot, r.page, r.pos) : make_int4(0, 0, 0, 0);
     }
   }
-  int total, mx, incl;
-  call_totals<kWeighted>(a, f, total, mx, incl);
-  const Plan plan = make_plan<Plan>(a, total, mx);
-  const long long start = plan.start_of(w);
-  if (start >= plan.total) return;
-  const long long end = plan.end_of(w);
-  int b, excl;
-  SeqPages sp;
-  locate<kWeighted>(a, f, incl, start, b, sp, excl);
-  if (b < 0) return;
-  const long long rel = start - (long long)excl * H;
-  int g = (int)udiv(rel, sp.len);
-  int j0 = first_page_at(sp, (int)(rel - (long long)g * sp.len));
-  while (true) {
-    const long long seg0 = (long long)excl * H + (long long)g * sp.len;
-    if (seg0 >= end) return;
-    const int j1 = end - seg0 >= sp.len ? sp.np : first_page_at(sp, (int)(end - seg0));
-    if (j0 < j1) attend_segment<D, G, kEntries, Plan>(a, w, b, g, j0, j1, sp, seg0, plan, q, n, s_ent);
-    if (j1 < sp.np) return;
-    j0 = 0;
-    if (++g == H) {                              // next sequence that holds any page
-      g = 0;
-      excl += sp.len;
-      do {
-        if (++b >= a.batch) return;
-        sp = seq_pages(a, f, b);
-      } while (sp.len == 0);
+  if constexpr (!kWeighted) {                      // few segments: worker wg takes one piece of one
+    const int total = __builtin_amdgcn_readlane(f.lane_incl, 63);
+    const int total_lo = __builtin_amdgcn_readlane(wave_inclusive_scan(f.lane_lo), 63);
+    const int u =
+        small_units((long long)total * H, (long long)total_lo * H, wave_max(f.lane_len), a.splits, a.min_pages, D);
+    const int cuts = f.lane_len > 0 ? small_pieces(f.lane_len, u) : 0, pieces = cuts + f.lane_x;
+    const int upto = wave_inclusive_scan(pieces);
+    const unsigned long long m = __ballot(wg < upto * H);
+    if (!m) return;
+    const int b = __ffsll((long long)m) - 1;
+    const SeqPages sp = seq_pages(a, f, b);
+    const int r = wg - __builtin_amdgcn_readlane(upto - pieces, b) * H;
+    const int p = (int)((uint32_t)r / (uint32_t)H), g = r - p * H;
+    int j0, j1;
+    small_piece(sp, __builtin_amdgcn_readlane(cuts, b), p, j0, j1);
+    if (j0 < j1) attend_segment<D, G, kEntries>(a, p, b, g, j0, j1, sp, q, n, s_ent);
+  } else {
+    int total, total_lo, mx, incl;
+    call_totals(a, f, total, total_lo, mx, incl);
+    // Few workers are spread over the workgroups, the first waves of each.
+    const int workers = stream_workers(total, total_lo, a.batch, D, a.attn_blocks, kEntries ? 1 : 2);
+    const int active = cdiv(workers, a.attn_blocks / kWpb);
+    if (wv >= active) return;
+    const int w = uni(wg * active + wv);
+    const WeightedPlan plan =
+        stream_plan_of<kWpb>((long long)total * H, mx, a.splits, a.min_pages, workers, PASK_ODD_WEIGHT);
+    const long long start = plan.start_of(w);
+    if (start >= plan.total) return;
+    const long long end = plan.end_of(w);
+    int b, excl;
+    SeqPages sp;
+    locate(a, f, incl, start, b, sp, excl);
+    if (b < 0) return;
+    const long long rel = start - (long long)excl * H;
+    int g = (int)udiv(rel, sp.len);
+    int j0 = first_page_at(sp, (int)(rel - (long long)g * sp.len));
+    while (true) {
+      const long long seg0 = (long long)excl * H + (long long)g * sp.len;
+      if (seg0 >= end) return;
+      const int j1 = end - seg0 >= sp.len ? sp.np : first_page_at(sp, (int)(end - seg0));
+      if (j0 < j1)
+        attend_segment<D, G, kEntries>(a, (int)(w - plan.block_of(seg0)), b, g, j0, j1, sp, q, n, s_ent);
+      if (j1 < sp.np) return;
+      j0 = 0;
+      if (++g == H) {                              // next sequence that holds any page
+        g = 0;
+        excl += sp.len;
+        do {
+          if (++b >= a.batch) return;
+          sp = seq_pages(a, f, b);
+        } while (sp.len == 0);
+      }
     }
   }
 }
@@ -1246,10 +1245,9 @@ __global__ __launch_bounds__(64) void attn_merge_sliced_kernel(AttnArgs a) {
   const size_t blk0 = (size_t)seg * a.splits;
   PieceMerge<D, G, kSlicedBatch> pm;
   constexpr int kB = kSlicedBatch;
-  // Before the piece count is known: slots up to the most a segment can have
-  // (the ranges' 1/PASK_SMALL_PIECES floor), not the workspace's last, so the
-  // loads past the count re-read one slot instead of stale partials.
-  pm.load(a, blk0, t, q, j, min(a.splits, PASK_SMALL_PIECES + 1) - 1, 4);
+  // With the piece count: slots below `splits` are in bounds; those past the
+  // count are skipped.
+  pm.load(a, blk0, t, q, j, a.splits - 1, 4);
   const int nparts = pieces_of(a, b, g);
   if (nparts == 0) {
 #pragma unroll
@@ -1432,12 +1430,12 @@ hipError_t launch_attention(const AttnArgs& args, int group_size, hipStream_t s)
   const int D = args.cv.head_dim;
   AttnArgs a = args;
   const int segs = a.batch * a.cv.n_kv_heads;
-  const bool small = segs <= kSmallSegments;
+  const bool small = a.batch <= 64 && segs <= kAlignedSegments;
   if (a.tags_new && (a.batch > kFusedMaxBatch || a.cv.window != 0 || a.ws_seq == nullptr)) return hipErrorInvalidValue;
   const int extra = a.tags_new ? (a.batch + 63) / 64 : 0;   // merge blocks that enter the step's entries
 #define PASK_CASE(DD, GG)                                                        \
   if (D == DD && group_size == GG) {                                             \
-    a.attn_blocks = small ? attn_grid<DD, GG, false>() : attn_grid<DD, GG, true>(); \
+    a.attn_blocks = small ? small_low_workers(DD) + 2 * segs : attn_grid<DD, GG, true>(); \
     if (a.attn_blocks <= 0) return hipErrorInvalidDeviceFunction;                \
     a.min_pages = small ? kSmallMinPages : kMinPagesPerBlock;                    \
     if (small) {                                                                 \

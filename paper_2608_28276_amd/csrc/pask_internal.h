@@ -18,35 +18,19 @@ constexpr int kCounterStride = 8;
 constexpr int kPage = 16;          // tokens per page
 constexpr int kQGroup = 32;        // elements per fp16 scale of a RETAIN-LOW vector
 // Range an attention worker on an odd-numbered XCD takes, in sixteenths of
-// an even-XCD worker's: measured per-XCD finish times show the odd XCDs
-// streaming pages about 10% slower (two boxes, every call).  With four
-// workers per workgroup 15 and 14 tie on the batch-64 Qwen3-4B call, 15 is
-// 2% faster on the int4-heavy prompt-side call and 0.4% slower on the
-// Qwen3-32B-shaped one; 13 is slower on all.  Equal ranges (16) measured
-// 1.8% slower on the batch-64 call (202.6 against 198.9 us, interleaved in
-// one process), and so did ranges left to chunks taken at run time from a
-// counter (2/16 of the work: 208.7 us; 4/16: 218.0 us).
+// an even-XCD worker's (calls with more than kAlignedSegments segments).
+// Equal ranges: with 512 workers streaming (stream_workers) 15 measured 4%
+// slower at batch 64 (195.0 against 188.0 us), and with all 2,048 5% slower on
+// an int4-heavy history (112.7 against 107.2 us).
 #ifndef PASK_ODD_WEIGHT
-#define PASK_ODD_WEIGHT 15
+#define PASK_ODD_WEIGHT 16
 #endif
 // Stream-K workers (single waves) per workgroup of the attention kernel for
-// calls with more than 64 segments: 2,048 single-wave workgroups took 4.5 us
-// to dispatch; four waves per workgroup measured 0.7% faster at batch 64.
+// those calls: 2,048 single-wave workgroups took 4.5 us to dispatch; two waves
+// per workgroup measured as four on HIGH pages and 5% slower on LOW pages
+// (112.7 against 107.2 us at 87% LOW).
 #ifndef PASK_ATTN_WPB
 #define PASK_ATTN_WPB 4
-#endif
-// Calls with at most 64 (sequence, KV head) segments take ranges of at least
-// 1/PASK_SMALL_PIECES of the longest segment, so no segment is cut into more
-// than PASK_SMALL_PIECES + 1 pieces (the ranges grow instead).  Interleaved in one
-// process, per call at Qwen3-4B geometry with prompts U{1024..8192} against
-// no cap (pieces of 4 pages): 2 sequences 25.0 -> 20.7 us, 3: 26.5 -> 21.2,
-// 4: 30.2 -> 25.4, 6: 33.5 -> 29.4, 8: 38.3 -> 36.9, one sequence 17.5 ->
-// 16.1 us and one 2.3k-entry sequence unchanged (13.8 / 13.9 us); caps of 16,
-// 24 and 48 were each slower somewhere.  Fewer, longer workers carry less of
-// the per-worker fixed cost (plan, q loads, block tables, partial rows) and
-// leave fewer partials to merge.
-#ifndef PASK_SMALL_PIECES
-#define PASK_SMALL_PIECES 32
 #endif
 #ifndef PASK_UNIT_TOKENS
 #define PASK_UNIT_TOKENS 128
@@ -135,12 +119,17 @@ struct AttnArgs {
   int32_t min_pages;        // fewest pages a worker takes (HIGH-page weight), set at launch
 };
 
-// Calls with at most kSmallSegments (sequence, KV head) segments cut them
-// finer (pieces down to kSmallMinPages pages, the workspace holding up to
-// kSmallPartials partials in all) and merge each segment's pieces with
-// several thread groups at once.
+// The workspace of calls with at most kSmallSegments (sequence, KV head)
+// segments holds pieces down to one page, up to kSmallPartials partials in all.
 constexpr int kSmallSegments = 64;
 constexpr int kSmallPartials = 4096;
+// Calls with at most kAlignedSegments segments (and at most 64 sequences) cut
+// every segment by itself and merge its pieces with several thread groups at
+// once (small_units in pask_plan.h).  At 256 segments the cuts are too coarse
+// to even out ragged ones: 32 sequences of 1,000-8,000 entries take 106.7 us
+// so, 98.0 by ranges over the whole list; 16 take 54.4 and 55.0, 9 of 4,064
+// 30.6 and 34.8.
+constexpr int kAlignedSegments = 128;
 // Calls that persist their step's entry themselves: every workgroup decides
 // the entries of all sequences, 64 at a time (one per lane of a wave), and
 // keeps their counts and outcomes in LDS (32 bytes per sequence, two

@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <math.h>
 #include <stdint.h>
 
 namespace pask {
@@ -59,6 +60,8 @@ __host__ __device__ __forceinline__ SeqPages make_pages(int n_hi, int n_win, int
   s.len = len_of(n_hi, n_win, n_lo, n_x);
   return s;
 }
+// Units of a LOW store of n_lo slots.
+__host__ __device__ __forceinline__ int low_len_of(int n_lo) { return kUnit * cdiv(n_lo, 16); }
 // Unit offset of page j inside its segment.
 __host__ __device__ __forceinline__ int page_start(const SeqPages&, int j) { return kUnit * j; }
 // First page whose unit offset is >= u (s.np when there is none).
@@ -133,8 +136,26 @@ __host__ __device__ __forceinline__ StreamPlan<kWpb> stream_plan_of(long long to
   return p;
 }
 
-// The same split with equal ranges of U units, for calls with at most 64
-// segments (latency-bound: a few pages per worker).
+// Workers such a call uses of the `limit` resident ones (`share` calls run on
+// them at once).  Most of the history HIGH and long: 512 at head_dim 128, 1,024
+// at 64, two per compute unit and one, with 8 MiB of pages in flight; more
+// waves only lengthen the memory's queues (64 sequences, 8 KV heads, D 128,
+// prompts of 1,024-8,192 tokens and 512 generated: 208.8 us with all 2,048,
+// 203.5 with 1,024, 194.7 with 512, 209.8 with 768 and 242 with 384, which
+// leave compute units unevenly loaded; prompts of 4,000: 175.9 -> 160.3).
+// LOW pages are bound by the latency of their arithmetic and want every wave
+// (61% LOW: 231 us with 512, 172 with all; 15%: 205.8 and 210.6; 19%: even),
+// and so do calls of many short segments, a few of which each worker would
+// take in turn (384 sequences, 26 pages a segment: 148 us with 512, 138 with all).
+__host__ __device__ __forceinline__ int stream_workers(int total, int total_lo, int batch, int head_dim, int limit,
+                                                       int share) {
+  if (total_lo >= total / 6 || total / kUnit < 64 * batch) return limit;
+  const int few = 512 * 128 / head_dim / share;
+  return few < limit ? few : limit;
+}
+
+// Equal ranges of U units.  Calls with few segments split every segment so, by
+// itself, with unit 0 at its first page (small_piece).
 struct EvenPlan {
   long long total;   // units
   int U;             // units per worker
@@ -155,6 +176,54 @@ __host__ __device__ __forceinline__ EvenPlan even_plan_of(long long total, int m
   if (lo1 > U) U = lo1;
   p.U = U;
   return p;
+}
+
+// Calls with at most kAlignedSegments segments: every segment is cut by itself
+// into pieces of about small_units units, one worker each, so no worker
+// crosses into another segment, where it would start its page stream anew
+// (ranges over the whole list, one sequence of 4,064 entries, 8 KV heads, D 128:
+// 33 pieces of 8 pages that happened to end at the segment's end 13.8 us per
+// call, 37 of 7 pages 15.5, 26 of 10 16.8).  A piece is at least min_pages and
+// 3/8 of the square root of the segment's pages (longer pieces leave fewer
+// partials to merge), and the call has at most 512 pieces of HIGH pages or
+// 1,536 of LOW pages at D 128, twice that at D 64 (see stream_workers).  Per
+// call, ranges of at least 1/32 of the longest segment -> this: one sequence of
+// 264 / 2,064 / 8,064 / 32,064 entries 11.6 / 13.2 / 18.7 / 42.0 -> 9.9 / 11.8 /
+// 17.7 / 30.0 us, 8 of 1,064 18.3 -> 15.4; against ranges over the whole list
+// with 2,048 workers: 9 of 4,064 43.3 -> 30.7, 16 of 512-2,112 31.8 -> 22.6.
+__host__ __device__ constexpr int small_low_workers(int head_dim) { return 1536 * 128 / head_dim; }
+// Units a piece of such a call should have.  total, mx (of stored pages),
+// splits, min_pages: as for stream_plan_of; total_lo: the units of LOW pages
+// among the total.
+__host__ __device__ __forceinline__ int small_units(long long total, long long total_lo, int mx, int splits,
+                                                    int min_pages, int head_dim) {
+  int u = kUnit * min_pages;
+  const int n = small_low_workers(head_dim);
+  const int lo1 = cdiv(mx, splits > 2 ? splits - 2 : 1), lo2 = (int)udiv(3 * total - 2 * total_lo + n - 1, n);
+  const int lo3 = (int)(12.0f * sqrtf((float)(mx / kUnit)));
+  u = lo1 > u ? lo1 : u;
+  u = lo2 > u ? lo2 : u;
+  return lo3 > u ? lo3 : u;
+}
+// Pieces that len units of stored pages are cut into for pieces of about u
+// units; the step's own entry is one piece more, the segment's last (beside
+// stored pages it made its worker the call's slowest: one sequence of 2,048
+// entries 12.4 us, 9.3 so).
+__host__ __device__ __forceinline__ int small_pieces(int len, int u) { return (int)udiv(len + u - 1, u); }
+// The pages [j0, j1) of piece p of a segment cut into n pieces of stored pages.
+// None is empty: rounding a piece's units up moves the last one's start by less
+// than n units, and a piece has at least 31 + n (small_units: 64 for n <= 33,
+// else about 4.5 n by the square root).
+__host__ __device__ __forceinline__ void small_piece(const SeqPages& s, int n, int p, int& j0, int& j1) {
+  if (p == n) {
+    j0 = s.np_l;
+    j1 = s.np;
+    return;
+  }
+  const EvenPlan e = even_plan_of(kUnit * s.np_l, kUnit * s.np_l, n + 1, 1, n);
+  const int a = first_page_at(s, (int)e.start_of(p)), b = first_page_at(s, (int)e.end_of(p));
+  j0 = a < s.np_l ? a : s.np_l;
+  j1 = b < s.np_l ? b : s.np_l;
 }
 
 // Pieces of the segment starting at unit seg0 with pages sp (sp.np > 0).

@@ -160,3 +160,23 @@ def test_decode_call_of_many_sequences(B):
     for t in range(2):
         sc.decode_step(t)
     sc.check_state()
+
+
+@pytest.mark.parametrize("B,Hkv,D", [(16, 8, 128), (17, 8, 128), (18, 7, 64), (64, 2, 64), (64, 3, 64)])
+def test_decode_call_around_few_segments(B, Hkv, D):
+    """128 (sequence, KV head) segments and fewer are cut one by one, more as
+    ranges over the whole list, whose workers are few when the history is long
+    and HIGH: lengths from 0 to 70 pages, so that segments have one to several
+    pieces, and one sequence of 1,900 tokens; both stores; two steps."""
+    say(f"case: decode of {B} x {Hkv} segments, D={D}")
+    pol = make_policy(6, 1, 1, 0.4, seed=B + Hkv)
+    P = [(97 * b) % 1100 for b in range(B)]
+    P[-1] = 1900
+    base = function_call_tags(B + 40, 6)
+    tags = np.stack([base[b:b + 40] for b in range(B)])
+    sc = Scenario(pol, B=B, L=1, Hq=2 * Hkv, Hkv=Hkv, D=D, prompt_lens=P, gen_tags=tags, seed=B)
+    sc.fill_prompt()
+    sc.append_steps(0, 38)
+    sc.decode_step(38)
+    sc.decode_step(39)
+    sc.check_state()
