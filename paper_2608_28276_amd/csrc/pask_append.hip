@@ -28,7 +28,6 @@
 namespace pask {
 namespace {
 
-constexpr int kPackTokens = 16;   // tokens per block of the recent-window fill kernel
 
 // A 16-byte piece of a page a bulk append writes once (read only by later
 // attention calls): non-temporal, so the stream does not displace other lines
@@ -986,109 +985,6 @@ __global__ __launch_bounds__(kPackThreads) void append_pack_page_kernel(AppendAr
   }
 }
 
-// One token of sequence b (thread 0 of the block): its action (Eq. 10, or
-// the online controller when parser states are given).
-__device__ __forceinline__ int decide_one(const AppendArgs& a, const uint8_t* s_a0, const uint8_t* s_amin, int b,
-                                          int32_t* cnt, int pos, bool& forced, uint32_t& flags) {
-  const CacheView& cv = a.cv;
-  const int tag = a.tags ? (int)a.tags[(size_t)b * a.max_new] : 0;
-  bool bad;
-  int act = decide(s_a0, s_amin, a.tab.n_tags, a.tab.n_sink, (a.flags & kKeepAll) != 0u, tag, pos, forced, bad);
-  if (bad) flags |= PASK_FLAG_BAD_TAG;
-  if (a.states) {
-    if (cv.budget->loaded == kBudgetLoaded) {
-      int64_t* r = budget_of(cnt);
-      int64_t R = *r;
-      act = budget_decide(cv.budget, tag, (int)a.states[(size_t)b * a.max_new], forced, (int)a.tab.group, R, flags);
-      *r = R;
-    } else {
-      flags |= PASK_FLAG_NO_BUDGET;
-    }
-  }
-  return act;
-}
-
-// Persist step of one entry at position pos (thread 0): DROP is counted; a
-// kept entry takes the next slot of its store (a new page when the slot
-// starts one) and its index-list entry.  Returns the store code (store << 30
-// | slot) and the page, or -1 when the entry is not stored.
-__device__ __forceinline__ int slot_one(const CacheView& cv, int b, int layer, int32_t* cnt, int act, bool forced,
-                                        int pos, int& page, uint32_t& flags) {
-  if (act == kDrop) {
-    cnt[kCntDrop] += 1;
-    return -1;
-  }
-  const int st = act == kHigh ? kHi : kLo;
-  const int slot = cnt[st];
-  int32_t* bt = block_table_of(cv, b, layer, st);
-  if (slot % kPage == 0) {
-    const unsigned pid = atomicAdd(&cv.status[2 + st], 1u);
-    const unsigned pool = st == kHi ? (unsigned)cv.hi_pages : (unsigned)cv.lo_pages;
-    if (pid >= pool) {
-      flags |= st == kHi ? PASK_FLAG_HI_POOL_EXHAUSTED : PASK_FLAG_LO_POOL_EXHAUSTED;
-      cnt[kCntLost] += 1;
-      return -1;
-    }
-    bt[slot / kPage] = (int)pid;
-  }
-  page = bt[slot / kPage];
-  index_list_of(cv, b, layer, st)[slot] = pos;
-  cnt[st] = slot + 1;
-  if (forced) cnt[kCntForced] += 1;
-  return (st << 30) | slot;
-}
-
-// One token per sequence: thread 0 decides and slots it, then the block
-// writes it.
-template <int D>
-__global__ __launch_bounds__(256) void append_step_kernel(AppendArgs a) {
-  __shared__ uint8_t s_a0[64], s_amin[64];
-  __shared__ int s_code, s_page;
-  const CacheView& cv = a.cv;
-  const int b = blockIdx.x;
-  load_table(a.tab, s_a0, s_amin);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t flags = 0;
-    const int n = clamp_n_new(a, b, flags);
-    int code = -1, page = -1;
-    if (n > 0) {
-      int32_t* cnt = counters_of(cv, b, a.layer);
-      const int pos = cnt[kCntPos];
-      if (pos >= cv.max_tokens) {
-        flags |= PASK_FLAG_SEQ_CAPACITY;
-        cnt[kCntLost] += 1;
-      } else {
-        bool forced;
-        const int act = decide_one(a, s_a0, s_amin, b, cnt, pos, forced, flags);
-        code = slot_one(cv, b, a.layer, cnt, act, forced, pos, page, flags);
-        cnt[kCntPos] = pos + 1;
-      }
-    }
-    if (flags) atomicOr(cv.status, flags);
-    s_code = code;
-    s_page = page;
-  }
-  __syncthreads();
-  const int code = s_code;
-  if (code < 0) return;
-  const size_t row = (size_t)cv.n_kv_heads * D;
-  const uint16_t* kin = a.k + (size_t)b * a.max_new * row;
-  const uint16_t* vin = a.v + (size_t)b * a.max_new * row;
-  const int slot = code & 0x3FFFFFFF;
-  if ((code >> 30) == kHi) write_hi<D>(cv, s_page, slot % kPage, kin, vin);
-  else write_lo<D>(cv, s_page, slot % kPage, kin, vin);
-}
-
-// ---------------------------------------------------------------------------
-// the protected recent window (Section 3.1)
-// ---------------------------------------------------------------------------
-// With W > 0 a token is decided when it is appended (its action and forced
-// flag go to ring_act, the controller charges it then) and enters the window
-// of its (sequence, layer): window slot p mod W, held in HIGH page layout in
-// pages of the HIGH pool reserved for the windows.  It is persisted by its
-// action when position p + W is appended.
-
 // The bf16 K and V rows [Hkv][D] of slot t of a HIGH-layout page (the
 // inverse of write_hi), into kout / vout, by the whole block.
 template <int D>
@@ -1113,9 +1009,144 @@ __device__ __forceinline__ void read_hi_token(const CacheView& cv, int page, int
   }
 }
 
+// One token of sequence b (thread 0 of the block): its action (Eq. 10, or
+// the online controller when parser states are given; R: the remaining budget).
+__device__ __forceinline__ int decide_one(const AppendArgs& a, const uint8_t* s_a0, const uint8_t* s_amin, int tag,
+                                          int state, uint32_t loaded, int pos, bool& forced, int64_t& R,
+                                          uint32_t& flags) {
+  const CacheView& cv = a.cv;
+  bool bad;
+  int act = decide(s_a0, s_amin, a.tab.n_tags, a.tab.n_sink, (a.flags & kKeepAll) != 0u, tag, pos, forced, bad);
+  if (bad) flags |= PASK_FLAG_BAD_TAG;
+  if (a.states) {
+    if (loaded == kBudgetLoaded) act = budget_decide(cv.budget, tag, state, forced, (int)a.tab.group, R, flags);
+    else flags |= PASK_FLAG_NO_BUDGET;
+  }
+  return act;
+}
+
+// The token of sequence b (one per sequence): 16 bytes of its K (threads
+// below 128) or V row (the others) per thread, at most 8 x 128 elements each.
+__device__ __forceinline__ uint4 row_piece(const AppendArgs& a, int b, int pieces) {
+  const int t = (int)threadIdx.x & 127;
+  if (t >= pieces) return make_uint4(0u, 0u, 0u, 0u);
+  const uint16_t* row = (threadIdx.x < 128 ? a.k : a.v) + (size_t)b * a.max_new * pieces * 8;
+  return *reinterpret_cast<const uint4*>(row + t * 8);
+}
+
+// One token per sequence (kWindow: which enters the recent window, the entry
+// at pos - W leaving it).  Thread 0 decides and slots; the block then writes.
+// The kernel is a chain of memory round trips, so everything that does not
+// wait for the decision is issued at its start - the token's rows, its tag,
+// the counters, then what the position gives: the leaving entry's window slot
+// and action, and the page of either store's next slot (64 sequences with
+// W = 64: 9.5 -> 8.4 us; 16 under the controller: 6.7 -> 6.4).
+template <int D, bool kWindow>
+__global__ __launch_bounds__(256) void append_step_kernel(AppendArgs a) {
+  __shared__ uint8_t s_a0[64], s_amin[64];
+  __shared__ int s_code, s_page, s_ws;
+  __shared__ __align__(16) uint16_t s_new[2][8 * D];
+  __shared__ __align__(16) uint16_t s_old[kWindow ? 2 : 1][kWindow ? 8 * D : 1];
+  const CacheView& cv = a.cv;
+  const int b = blockIdx.x;
+  const int H = cv.n_kv_heads, pieces = H * D / 8;
+  uint32_t flags = 0;
+  const int n = clamp_n_new(a, b, flags);
+  int32_t* cnt = counters_of(cv, b, a.layer);
+  const int4 c0 = *reinterpret_cast<const int4*>(cnt), c1 = *reinterpret_cast<const int4*>(cnt + 4);
+  const int tag = a.tags ? (int)a.tags[(size_t)b * a.max_new] : 0;
+  const int state = a.states ? (int)a.states[(size_t)b * a.max_new] : 0;
+  const uint32_t loaded = a.states ? cv.budget->loaded : 0u;
+  const uint4 mine = row_piece(a, b, pieces);
+  load_table(a.tab, s_a0, s_amin);
+  const int pos = c0.z;
+  const int W = kWindow ? cv.window : 1, ws = kWindow ? pos % W : 0;
+  const int rpage = kWindow ? (b * cv.n_layers + a.layer) * cv.ring_pp + ws / kPage : 0;
+  const bool leaves = kWindow && pos >= W;         // position pos - W leaves the window
+  const int last = cv.max_pages - 1;
+  const int bt_hi = block_table_of(cv, b, a.layer, kHi)[min(c0.x / kPage, last)];
+  const int bt_lo = block_table_of(cv, b, a.layer, kLo)[min(c0.y / kPage, last)];
+  uint8_t* ract = kWindow ? ring_act_of(cv, b, a.layer) + ws : nullptr;
+  const int old = leaves ? (int)*ract : 0;
+  if (leaves) read_hi_token<D>(cv, rpage, ws % kPage, s_old[0], s_old[1]);
+  if (((int)threadIdx.x & 127) < pieces)
+    *reinterpret_cast<uint4*>(&s_new[threadIdx.x >> 7][((int)threadIdx.x & 127) * 8]) = mine;
+  __syncthreads();                                 // s_a0 / s_amin (and the rows)
+  if (threadIdx.x == 0) {
+    int code = -1, page = -1;
+    const bool fits = n > 0 && pos < cv.max_tokens;
+    if (n > 0 && !fits) {
+      flags |= PASK_FLAG_SEQ_CAPACITY;
+      cnt[kCntLost] = c1.y + 1;
+    }
+    if (fits) {
+      bool forced;
+      int64_t R = ((int64_t)c1.w << 32) | (uint32_t)c1.z;
+      int act = decide_one(a, s_a0, s_amin, tag, state, loaded, pos, forced, R, flags);
+      if (a.states && loaded == kBudgetLoaded) *budget_of(cnt) = R;
+      cnt[kCntPos] = pos + 1;
+      int at = pos;                                // the entry to persist now, if any
+      if constexpr (kWindow) {
+        *ract = (uint8_t)(act | (forced ? 4 : 0));
+        act = old & 3;
+        forced = ((old >> 2) & 1) != 0;
+        at = pos - W;
+      }
+      if (!kWindow || leaves) {
+        if (act == kDrop) {
+          cnt[kCntDrop] = c0.w + 1;
+        } else {                                   // the next slot of its store, a new page when it opens one
+          const int st = act == kHigh ? kHi : kLo;
+          const int slot = st == kHi ? c0.x : c0.y;
+          page = st == kHi ? bt_hi : bt_lo;
+          bool stored = true;
+          if (slot % kPage == 0) {
+            const unsigned pid = atomicAdd(&cv.status[2 + st], 1u);
+            stored = pid < (unsigned)(st == kHi ? cv.hi_pages : cv.lo_pages);
+            page = (int)pid;
+            if (stored) block_table_of(cv, b, a.layer, st)[slot / kPage] = page;
+          }
+          if (stored) {
+            index_list_of(cv, b, a.layer, st)[slot] = at;
+            cnt[st] = slot + 1;
+            if (forced) cnt[kCntForced] = c1.x + 1;
+            code = (st << 30) | slot;
+          } else {
+            flags |= st == kHi ? PASK_FLAG_HI_POOL_EXHAUSTED : PASK_FLAG_LO_POOL_EXHAUSTED;
+            cnt[kCntLost] = c1.y + 1;
+          }
+        }
+      }
+    }
+    if (flags) atomicOr(cv.status, flags);
+    s_code = code;
+    s_page = page;
+    s_ws = fits ? ws : -1;
+  }
+  __syncthreads();                                 // also: the leaving entry is read before its slot is reused
+  const int code = s_code;
+  const int slot = code & 0x3FFFFFFF;
+  const uint16_t* kin = kWindow ? s_old[0] : s_new[0];
+  const uint16_t* vin = kWindow ? s_old[kWindow ? 1 : 0] : s_new[1];
+  if (kWindow && s_ws >= 0) write_hi<D>(cv, rpage, ws % kPage, s_new[0], s_new[1]);
+  if (code < 0) return;
+  if ((code >> 30) == kHi) write_hi<D>(cv, s_page, slot % kPage, kin, vin);
+  else write_lo<D>(cv, s_page, slot % kPage, kin, vin);
+}
+
+// ---------------------------------------------------------------------------
+// the protected recent window (Section 3.1)
+// ---------------------------------------------------------------------------
+// With W > 0 a token is decided when it is appended (its action and forced
+// flag go to ring_act, the controller charges it then) and enters the window
+// of its (sequence, layer): window slot p mod W, held in HIGH page layout in
+// pages of the HIGH pool reserved for the windows.  It is persisted by its
+// action when position p + W is appended.
+
 // The new tokens that stay in the window (the last min(n_fit, W) of the
-// call) into their window slots; after the pack kernel has read the slots
-// they replace.
+// call) into their window slots, a block per token; after the pack kernel has
+// read the slots they replace.  (16 tokens in turn per block left most of the
+// chip idle: 27.9 us for 64 sequences and W = 64, 17.3 so.)
 template <int D>
 __global__ __launch_bounds__(256) void append_window_fill_kernel(AppendArgs a) {
   const CacheView& cv = a.cv;
@@ -1123,72 +1154,12 @@ __global__ __launch_bounds__(256) void append_window_fill_kernel(AppendArgs a) {
   const int W = cv.window;
   const int32_t* stg = cv.staging + (size_t)b * cv.staging_stride;
   const int p0 = stg[cv.staging_stride - 2], n_fit = stg[cv.staging_stride - 1];
-  const int j0 = max(0, n_fit - W);
+  const int j = max(0, n_fit - W) + (int)blockIdx.x;
+  if (j >= n_fit) return;
   const size_t row = (size_t)cv.n_kv_heads * D;
-  for (int kk = 0; kk < kPackTokens; ++kk) {
-    const int j = j0 + (int)blockIdx.x * kPackTokens + kk;
-    if (j >= n_fit) break;
-    const int ws = (p0 + j) % W;
-    write_hi<D>(cv, ring_page(cv, b, a.layer, ws / kPage), ws % kPage, a.k + ((size_t)b * a.max_new + j) * row,
-                a.v + ((size_t)b * a.max_new + j) * row);
-  }
-}
-
-// One token per sequence with a window: thread 0 decides the new token and,
-// when position pos - W leaves the window, slots that entry by its recorded
-// action; the block then reads the leaving entry from its window slot into
-// LDS, writes the new token into that slot, and persists the leaving entry.
-template <int D>
-__global__ __launch_bounds__(256) void append_step_window_kernel(AppendArgs a) {
-  __shared__ uint8_t s_a0[64], s_amin[64];
-  __shared__ int s_code, s_page, s_ws;
-  __shared__ __align__(16) uint16_t s_kv[2][8 * D];
-  const CacheView& cv = a.cv;
-  const int b = blockIdx.x;
-  const int W = cv.window;
-  load_table(a.tab, s_a0, s_amin);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t flags = 0;
-    const int n = clamp_n_new(a, b, flags);
-    int code = -1, page = -1, ws = -1;
-    if (n > 0) {
-      int32_t* cnt = counters_of(cv, b, a.layer);
-      const int pos = cnt[kCntPos];
-      if (pos >= cv.max_tokens) {
-        flags |= PASK_FLAG_SEQ_CAPACITY;
-        cnt[kCntLost] += 1;
-      } else {
-        bool forced;
-        const int act = decide_one(a, s_a0, s_amin, b, cnt, pos, forced, flags);
-        uint8_t* ract = ring_act_of(cv, b, a.layer);
-        ws = pos % W;
-        if (pos >= W) {                              // position pos - W leaves the window
-          const uint8_t old = ract[ws];
-          code = slot_one(cv, b, a.layer, cnt, old & 3, ((old >> 2) & 1) != 0, pos - W, page, flags);
-        }
-        ract[ws] = (uint8_t)(act | (forced ? 4 : 0));
-        cnt[kCntPos] = pos + 1;
-      }
-    }
-    if (flags) atomicOr(cv.status, flags);
-    s_code = code;
-    s_page = page;
-    s_ws = ws;
-  }
-  __syncthreads();
-  const int code = s_code, ws = s_ws;
-  if (ws < 0) return;
-  const int rpage = ring_page(cv, b, a.layer, ws / kPage);
-  if (code >= 0) read_hi_token<D>(cv, rpage, ws % kPage, s_kv[0], s_kv[1]);
-  __syncthreads();                                   // the leaving entry is read before its slot is reused
-  const size_t row = (size_t)cv.n_kv_heads * D;
-  write_hi<D>(cv, rpage, ws % kPage, a.k + (size_t)b * a.max_new * row, a.v + (size_t)b * a.max_new * row);
-  if (code >= 0) {
-    const int slot = code & 0x3FFFFFFF;
-    if ((code >> 30) == kHi) write_hi<D>(cv, s_page, slot % kPage, s_kv[0], s_kv[1]);
-    else write_lo<D>(cv, s_page, slot % kPage, s_kv[0], s_kv[1]);
-  }
+  const int ws = (p0 + j) % W;
+  write_hi<D>(cv, ring_page(cv, b, a.layer, ws / kPage), ws % kPage, a.k + ((size_t)b * a.max_new + j) * row,
+              a.v + ((size_t)b * a.max_new + j) * row);
 }
 
 }  // namespace
@@ -1214,7 +1185,7 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t s) {
     else append_plan_kernel<false, true><<<dim3(a.batch), dim3(kPlanThreads), 0, s>>>(a);
     // pages of a store this call's leaving entries (at most max_new + W) can reach
     const dim3 gp((a.max_new + a.cv.window + kPage - 1) / kPage + 1, 2, a.batch);
-    const dim3 gf((std::min(a.max_new, a.cv.window) + kPackTokens - 1) / kPackTokens, a.batch);
+    const dim3 gf(std::min(a.max_new, a.cv.window), a.batch);
     if (a.cv.head_dim == 64) {
       append_pack_page_kernel<64><<<gp, dim3(kPackThreads), 0, s>>>(a);
       append_window_fill_kernel<64><<<gf, dim3(256), 0, s>>>(a);
@@ -1235,12 +1206,12 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t s) {
 
 hipError_t launch_append_step(const AppendArgs& a, hipStream_t s) {
   if (a.cv.window > 0) {
-    if (a.cv.head_dim == 64) append_step_window_kernel<64><<<dim3(a.batch), dim3(256), 0, s>>>(a);
-    else append_step_window_kernel<128><<<dim3(a.batch), dim3(256), 0, s>>>(a);
+    if (a.cv.head_dim == 64) append_step_kernel<64, true><<<dim3(a.batch), dim3(256), 0, s>>>(a);
+    else append_step_kernel<128, true><<<dim3(a.batch), dim3(256), 0, s>>>(a);
     return hipGetLastError();
   }
-  if (a.cv.head_dim == 64) append_step_kernel<64><<<dim3(a.batch), dim3(256), 0, s>>>(a);
-  else append_step_kernel<128><<<dim3(a.batch), dim3(256), 0, s>>>(a);
+  if (a.cv.head_dim == 64) append_step_kernel<64, false><<<dim3(a.batch), dim3(256), 0, s>>>(a);
+  else append_step_kernel<128, false><<<dim3(a.batch), dim3(256), 0, s>>>(a);
   return hipGetLastError();
 }
 
