@@ -143,9 +143,9 @@ __device__ __forceinline__ int64_t* budget_of(int32_t* cnt) {
 }
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-// Lanes below this one in a ballot.
-__device__ __forceinline__ int lanes_below(unsigned long long m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+// base + the lanes below this one in a ballot.
+__device__ __forceinline__ int lanes_below(unsigned long long m, int base) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
 }
 
 __device__ __forceinline__ void load_table(const TableColumn& tab, uint8_t* s_a0, uint8_t* s_amin) {
@@ -406,10 +406,14 @@ __global__ __launch_bounds__(kPlanThreads) void append_plan_kernel(AppendArgs a)
           e[r] = t;
           if (x < n_x && (t & kEntBad)) flags |= PASK_FLAG_BAD_TAG;
         }
-        wt.x += __popcll(__ballot(x < n_out && (e[r] & 3u) == kHigh));
-        wt.y += __popcll(__ballot(x < n_out && (e[r] & 3u) == 1u));
+        wt.x += __popcll(__builtin_amdgcn_ballot_w64(x < n_out && (e[r] & 3u) == kHigh));
+        wt.y += __popcll(__builtin_amdgcn_ballot_w64(x < n_out && (e[r] & 3u) == 1u));
       }
     }
+    // No code: every tag has arrived here, so the rounds below, whose stores are
+    // in flight, wait for no load (they waited for all stores, round after round).
+#pragma unroll
+    for (int r = 0; r < kPlanRounds; ++r) asm volatile("" : "+v"(e[r]));
     if (lane == 0) s_wave[wave] = wt;
     __syncthreads();
     int rank[2] = {0, 0}, tot[2] = {0, 0};
@@ -451,8 +455,9 @@ __global__ __launch_bounds__(kPlanThreads) void append_plan_kernel(AppendArgs a)
       if (r < rounds) {
         const int x = x0 + 64 * r;
         const bool hi = x < n_out && (e[r] & 3u) == kHigh, lo = x < n_out && (e[r] & 3u) == 1u;
-        const unsigned long long mh = __ballot(hi), ml = __ballot(lo);
-        const int slot = hi ? next[0] + lanes_below(mh) : next[1] + lanes_below(ml);
+        const unsigned long long mh = __builtin_amdgcn_ballot_w64(hi), ml = __builtin_amdgcn_ballot_w64(lo);
+        const int slot_hi = lanes_below(mh, next[0]), slot_lo = lanes_below(ml, next[1]);
+        const int slot = hi ? slot_hi : slot_lo;
         if ((hi || lo) && slot < (hi ? cap[0] : cap[1])) {
           il[hi ? slot : cv.max_tokens + slot] = e0 + x;
           if (slot % kPage == 0)
