@@ -1223,16 +1223,21 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {   // merg
 }
 
 // The same merge for calls with few segments, whose segments hold many
-// pieces: the merge of one segment is spread over NM * G4 / 4 single-wave
-// blocks (one per 16 float4 positions of the partial rows: query heads
-// 4q..4q+3 at dims 16k..16k+15), so the pieces' bytes are read by many CUs.
-// Lane 16j + n merges position n of the block over the pieces p = j (mod 4);
-// the four lane groups are then combined across lanes.
-constexpr int kSlicedBatch = 12;                 // pieces per lane group and round
-template <int D, int G>
+// pieces: the merge of one segment is spread over single-wave blocks, one per
+// kPos float4 positions of the partial rows, so the pieces' bytes are read by
+// many CUs.  Lane kPos j + n merges position n of the block over the pieces
+// p = j (mod 64 / kPos); the lane groups are then combined across lanes.
+// kPos 4 for the fewest segments: 64 pieces are in flight at once where kPos 16
+// takes 48, and a lane folds a quarter as many in series.  One sequence, 8 KV
+// heads, D 128, whole call with kPos 16 / 4: 2,064 entries 11.9 / 11.5 us, 8,064
+// 18.2 / 15.8, 32,064 with 91% LOW 24.5 / 20.9; but 264 entries 9.9 / 10.4 (few
+// pieces: the hint's splits say so), 8 sequences of 1,064 15.3 / 16.8.
+constexpr int kFineMergeSegments = 8, kFineMergeSplits = 64;
+template <int D, int G, int kPos>
 __global__ __launch_bounds__(64) void attn_merge_sliced_kernel(AttnArgs a) {
-  constexpr int NM = D / 16, X = merge_threads<D, G>() / 16;
-  const int lane = threadIdx.x, j = lane >> 4, n = lane & 15;
+  constexpr int NM = D / 16, X = merge_threads<D, G>() / kPos;
+  constexpr int kGroups = 64 / kPos, kB = kPos == 4 ? 4 : 12;   // pieces per lane group and round
+  const int lane = threadIdx.x, j = lane / kPos;
   const int H = a.cv.n_kv_heads;
   const int seg = uni(blockIdx.x / X), x = uni(blockIdx.x % X);
   if (seg >= a.batch * H) {                        // the extra block: the step's entries (at most 64 sequences)
@@ -1240,30 +1245,32 @@ __global__ __launch_bounds__(64) void attn_merge_sliced_kernel(AttnArgs a) {
     return;
   }
   const int b = seg / H, g = seg % H;
-  const int q = x / NM, k = x % NM, t = 16 * x + n;
+  const int t = kPos * x + lane % kPos, q = t / (NM * 16), k = (t / 16) % NM, n = t % 16;
   const size_t row0 = (size_t)b * a.n_q_heads + (size_t)g * G;
   const size_t blk0 = (size_t)seg * a.splits;
-  PieceMerge<D, G, kSlicedBatch> pm;
-  constexpr int kB = kSlicedBatch;
+  PieceMerge<D, G, kB> pm;
   // With the piece count: slots below `splits` are in bounds; those past the
   // count are skipped.
-  pm.load(a, blk0, t, q, j, a.splits - 1, 4);
+  pm.load(a, blk0, t, q, j, a.splits - 1, kGroups);
   const int nparts = pieces_of(a, b, g);
   if (nparts == 0) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (j == 0 && 4 * q + r < G) a.out[(row0 + 4 * q + r) * D + 16 * k + n] = 0;
-    if (a.lse && j == 0 && k == 0 && n < 4 && 4 * q + n < G) a.lse[row0 + 4 * q + n] = -INFINITY;
+    for (int r = 0; r < 4; ++r) {
+      if (j == 0 && 4 * q + r < G) {
+        a.out[(row0 + 4 * q + r) * D + 16 * k + n] = 0;
+        if (a.lse && k == 0 && n == 0) a.lse[row0 + 4 * q + r] = -INFINITY;
+      }
+    }
     return;
   }
   pm.init();
-  for (int p0 = 0; p0 < nparts; p0 += 4 * kB) {
+  for (int p0 = 0; p0 < nparts; p0 += kGroups * kB) {
     const int first = p0 + j;
-    if (p0 > 0) pm.load(a, blk0, t, q, first, nparts - 1, 4);
-    pm.fold(first < nparts ? (nparts - 1 - first) / 4 + 1 : 0);
+    if (p0 > 0) pm.load(a, blk0, t, q, first, nparts - 1, kGroups);
+    pm.fold(first < nparts ? (nparts - 1 - first) / kGroups + 1 : 0);
   }
 #pragma unroll
-  for (int off = 16; off <= 32; off *= 2) {      // lanes n, n+16, n+32, n+48
+  for (int off = kPos; off <= 32; off *= 2) {    // the lane groups
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float m2 = __shfl_xor(pm.M[r], off), l2 = __shfl_xor(pm.L[r], off), v2 = __shfl_xor(pm.acc[r], off);
@@ -1440,7 +1447,10 @@ hipError_t launch_attention(const AttnArgs& args, int group_size, hipStream_t s)
     a.min_pages = small ? kSmallMinPages : kMinPagesPerBlock;                    \
     if (small) {                                                                 \
       attn_kernel<DD, GG, false><<<dim3(a.attn_blocks), dim3(64), 0, s>>>(a);    \
-      attn_merge_sliced_kernel<DD, GG><<<dim3(segs * (merge_threads<DD, GG>() / 16) + extra), dim3(64), 0, s>>>(a); \
+      if (segs <= kFineMergeSegments && a.splits >= kFineMergeSplits)            \
+        attn_merge_sliced_kernel<DD, GG, 4><<<dim3(segs * (merge_threads<DD, GG>() / 4) + extra), dim3(64), 0, s>>>(a); \
+      else                                                                       \
+        attn_merge_sliced_kernel<DD, GG, 16><<<dim3(segs * (merge_threads<DD, GG>() / 16) + extra), dim3(64), 0, s>>>(a); \
     } else {                                                                     \
       attn_kernel<DD, GG, true><<<dim3(a.attn_blocks / kWpb), dim3(64 * kWpb), 0, s>>>(a); \
       attn_merge_kernel<DD, GG><<<dim3(segs + extra), dim3(merge_threads<DD, GG>()), 0, s>>>(a); \

@@ -180,3 +180,18 @@ def test_decode_call_around_few_segments(B, Hkv, D):
     sc.decode_step(38)
     sc.decode_step(39)
     sc.check_state()
+
+
+@pytest.mark.parametrize("G", [1, 4, 8])
+@pytest.mark.parametrize("n", [900, 17000])
+def test_merge_of_many_pieces(n, G):
+    """One sequence of few KV heads and many pages: the merge of the fewest
+    segments folds 64 pieces per round (17,000 tokens: more than one round)."""
+    say(f"case: merge of many pieces, n={n} G={G}")
+    pol = make_policy(6, 1, 1, 0.4, seed=G)
+    sc = Scenario(pol, B=1, L=1, Hq=2 * G, Hkv=2, D=64 if G == 1 else 128, prompt_lens=[n],
+                  gen_tags=function_call_tags(3, 9)[None], seed=n + G, max_ctx_hint=n + 600)
+    sc.fill_prompt()
+    for t in range(3):
+        sc.decode_step(t)
+    sc.check_state()
