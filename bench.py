@@ -237,7 +237,7 @@ def gpu_leg(cfg, P, tags, pol, steps: int, warmup: int, positions, states=None, 
         # One decode step: per layer, one pask_decode_attn call that persists the
         # step's token and attends the layer's history including it (the
         # attention and merge kernels persist the token themselves for at most
-        # 256 sequences without a recent window or parser states; otherwise the
+        # 1,024 sequences without a recent window or parser states; otherwise the
         # one-token append kernel runs first, inside the same call).
         sptr_ = sptr if stream is None else stream
         if tp is None:
@@ -574,18 +574,19 @@ def kernel_source_digest() -> str:
 
 def attn_kernels(cfg, window: int = 0, controller: bool = False) -> str:
     """The kernels of one pask_decode_attn call with its step's token: calls
-    with at most 64 (sequence, KV head) segments use the equal-range attention
-    and the sliced merge, larger ones the per-XCD weighted attention and the
-    merge; the one-token append kernel comes first when the call cannot
-    persist the token in those (more than 256 sequences, a recent window or
+    with at most 128 (sequence, KV head) segments cut every segment by itself
+    and use the sliced merge, larger ones take ranges over the whole page list
+    and the merge; the one-token append kernel comes first when the call cannot
+    persist the token in those (more than 1,024 sequences, a recent window or
     parser states)."""
     D, G = cfg.head_dim, cfg.group_size
-    if cfg.batch * cfg.n_kv_heads <= 64:
-        k = f"attn_kernel<{D}, {G}, false> + attn_merge_sliced_kernel<{D}, {G}>"
+    if cfg.batch <= 64 and cfg.batch * cfg.n_kv_heads <= 128:
+        positions = 4 if cfg.batch * cfg.n_kv_heads <= 8 else 16
+        k = f"attn_kernel<{D}, {G}, false> + attn_merge_sliced_kernel<{D}, {G}, {positions}>"
     else:
         k = f"attn_kernel<{D}, {G}, true> + attn_merge_kernel<{D}, {G}>"
-    if cfg.batch > 256 or window or controller:
-        k = f"append_step{'_window' if window else ''}_kernel<{D}> + " + k
+    if cfg.batch > 1024 or window or controller:
+        k = f"append_step_kernel<{D}, {'true' if window else 'false'}> + " + k
     return k
 
 
@@ -713,7 +714,7 @@ def main():
                        "generated_before_timing": args.t_start, "D": d["D"], "S_size": d["n_s"]},
             "roofline": {"bound": "hbm", "achieved": round(d["achieved"], 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(d["achieved"] / HBM_PEAK_GBS, 4), "traffic": None,
-                         "kernel": f"2 x attn_kernel<{cfg.head_dim}, {cfg.group_size}, true> + distortion_kernel "
+                         "kernel": f"attn_pair_kernel<{cfg.head_dim}, {cfg.group_size}> + distortion_kernel "
                                    "(one pask_attn_distortion call)",
                          "bytes_per_launch": round(d["call_bytes"]), "avg_launch_us": round(d["avg_call_us"], 2)},
             "cpu_baseline": None}), flush=True)
