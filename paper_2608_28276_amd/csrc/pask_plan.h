@@ -29,14 +29,15 @@ __host__ __device__ __forceinline__ long long udiv(long long a, long long b) {
 // weighting LOW pages by their bytes measured slower), so every page starts
 // at a multiple of kUnit.
 constexpr int kUnit = 32;
-// The page of the step's own entry weighs four pages: the worker that writes
-// and attends it does more than stream a page (its K / V rows are quantised,
-// stored and attended from registers).  Interleaved in one process against a
-// weight of one page: one Qwen3-4B-shaped sequence 13.3 / 13.3 us per call,
-// four sequences 28.1 against 29.3, the batch-64 call 203.5 against 204.8
-// (two pages: 13.3, 28.9, 203.7).
+// The page of the step's own entry weighs eight pages in the ranges of calls
+// with more than kAlignedSegments segments: the worker that writes and attends
+// it does more than stream a page (its K / V rows are quantised, stored and
+// attended from registers).  With weights of 1 / 2 / 4 / 8 pages, 64 sequences
+// of 1,024-8,192 kept tokens and 64 generated took 200.1 / 198.6 / 196.1 /
+// 192.5 us per call, 128 of 1,000-4,000 227.9 / 226.8 / 223.4 / 219.2, 64 with
+// 88% LOW 113.3 / 112.9 / 111.9 / 111.3, 384 of 64-768 151.6 / 150.7 / 149.7 / 151.1.
 #ifndef PASK_ENTRY_UNITS
-#define PASK_ENTRY_UNITS 128
+#define PASK_ENTRY_UNITS 256
 #endif
 constexpr int kEntryUnits = PASK_ENTRY_UNITS;
 struct SeqPages {
