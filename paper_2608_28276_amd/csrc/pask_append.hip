@@ -2,8 +2,9 @@
 //
 //   reset        zero the status word, page cursors and per-(sequence, layer)
 //                counters of a cache.
-//   append_plan  per sequence: the action of every new token (table column in
-//                LDS, the higher of selected action and floor, Eq. 10),
+//   append_plan  per sequence: the action of every new token (a table in LDS,
+//                the higher of selected action and floor, Eq. 10; or the online
+//                budget controller, Alg. 2),
 //                wavefront ballot + mbcnt prefix sums giving each surviving
 //                token its slot in the HIGH or LOW store in position order,
 //                page allocation, index lists and counters (the Persist step
@@ -11,11 +12,9 @@
 //   append_pack  copy RETAIN-HIGH K/V (bf16) or quantise-and-pack RETAIN-LOW
 //                K/V (int4, one fp16 scale per 32 elements) into the pages.
 //   append_step  both of the above for one token per sequence (decode).
-//   window       the protected recent window (Section 3.1): its plan, step
-//                and fill kernels (the bulk pack is append_pack, reading the
-//                entries that leave the window from their ring slots), and
-//                the online budget controller (Alg. 2) in the plan and step
-//                kernels.
+//   window       the protected recent window (Section 3.1) in the plan and step
+//                kernels and a fill kernel; append_pack reads the entries that
+//                leave the window from their ring slots.
 #include <hip/hip_runtime.h>
 
 #include <limits.h>

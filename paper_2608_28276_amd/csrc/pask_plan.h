@@ -71,14 +71,14 @@ __host__ __device__ __forceinline__ int first_page_at(const SeqPages& s, int u) 
   return j < s.np ? j : s.np;
 }
 
-// Calls with more than 64 (sequence, KV head) segments.  The work list is
+// Calls with many (sequence, KV head) segments.  The work list is
 // the segments (sequence b, KV head g) in that nesting order, each the units
 // of its pages.  Worker w (a wave; kWpb of them per workgroup) takes the
 // pages that start in its contiguous range [start_of(w), end_of(w)), of
-// weight(w) x step units.  Workgroups are dealt to the 8 XCDs in turn, and
-// the waves of the odd-numbered XCDs were measured streaming about 10%
-// slower, so a worker there weighs `odd` sixteenths against 16 on an even XCD
-// (16 when the ranges are at their minimum size: a latency-bound call).
+// weight(w) x step units.  Workgroups are dealt to the 8 XCDs in turn; a worker
+// on an odd-numbered one weighs `odd` sixteenths against 16 on an even one
+// (PASK_ODD_WEIGHT: equal; equal also when the ranges are at their minimum
+// size, a latency-bound call).
 // Every range is at least lo units, at least one page (pages start at
 // multiples of kUnit), so each range between the first and the last of a
 // segment holds a page of it, and no segment is cut into more than `splits`
