@@ -317,8 +317,7 @@ __global__ __launch_bounds__(kPlanThreads) void append_plan_kernel(AppendArgs a)
   const bool keep_all = (a.flags & kKeepAll) != 0u;
   if (threadIdx.x < 256) {
     const uint32_t z = threadIdx.x;
-    const int forced = kHigh | kEntForced;
-    int e = keep_all ? forced : forced | kEntBad;
+    int e = kHigh | kEntForced | (z < a.tab.n_tags ? 0 : kEntBad);
     if (!keep_all && z < a.tab.n_tags) {
       const int act = max((int)a.tab.a0[z], (int)a.tab.amin[z]);
       e = act == kDrop || act == kHigh ? act : 1;
@@ -363,7 +362,9 @@ __global__ __launch_bounds__(kPlanThreads) void append_plan_kernel(AppendArgs a)
     stg[cv.staging_stride - 2] = p0;
     stg[cv.staging_stride - 1] = n_fit;
   }
-  const uint8_t* tags = keep_all ? nullptr : a.tags + (size_t)b * a.max_new;
+  // A kept prompt may come without tags (every token then reads entry 0); the
+  // tags it does come with are still looked at for ones outside the table.
+  const uint8_t* tags = a.tags ? a.tags + (size_t)b * a.max_new : nullptr;
   const unsigned pool[2] = {(unsigned)cv.hi_pages, (unsigned)cv.lo_pages};
   __syncthreads();
 

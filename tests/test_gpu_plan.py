@@ -69,6 +69,46 @@ def test_bulk_plan_sizes(n, W):
         assert int(sess.counters()[b, 0, 2]) == z.size
 
 
+@pytest.mark.parametrize("W", [0, 5])
+@pytest.mark.parametrize("n", [1, 2, 40, 1025])
+@pytest.mark.parametrize("keep_all", [True, False])
+def test_tags_outside_the_table_are_reported(n, W, keep_all):
+    """A tag outside the table raises BAD_TAG however many tokens the call has,
+    whether the tokens are kept by their tags or all of them; a bad tag past
+    n_new, or past the sequence's capacity, is none."""
+    from paper_2608_28276_amd import pask
+    say(f"case: bad tag n={n} W={W} keep_all={keep_all}")
+    pol = make_policy(6, 1, 1, 0.4, 3)
+    pol.recent_window = W
+    room = 8                                         # the window fits the shortest sequence
+    put = lambda x: torch.as_tensor(x, device="cuda:0")
+    for z, at in ((5, n - 1), (6, n - 1), (255, 0), (6, n)):
+        sess = _session(pol, 1, 1, n + room)
+        tags = np.zeros((1, n + 1), np.uint8)
+        tags[0, at] = z
+        k = torch.ones((1, n + 1, H, D), dtype=torch.bfloat16, device=sess.device)
+        if at < n and n == 1:                        # one token: also the call without n_new
+            sess.append(0, put(tags[:, :1].copy()), k[:, :1].contiguous(), k[:, :1].contiguous(), keep_all=keep_all)
+        else:
+            sess.append(0, put(tags), k, k, n_new=put(np.array([n], np.int32)), keep_all=keep_all)
+        _, _, bad = oracle.decide(tags[0, :n], np.arange(n), 0, pol.action, pol.floor, pol.n_sink, keep_all)
+        assert sess.stats(batch=1)[0].device_flags == (pask.PASK_FLAG_BAD_TAG if bad.any() else 0), (z, at)
+        cnt = sess.counters()[0, 0].cpu().numpy()
+        assert int(cnt[2]) == n
+        if keep_all:
+            assert int(cnt[0]) == max(0, n - W)
+    sess = _session(pol, 1, 1, 30)                   # a bad tag of a token there is no room for
+    tags = np.zeros((1, 40), np.uint8)
+    tags[0, 35] = 77
+    k = torch.ones((1, 40, H, D), dtype=torch.bfloat16, device=sess.device)
+    if n == 40:
+        with pytest.raises(Exception):
+            sess.append(0, put(tags), k, k, keep_all=keep_all)   # more than a sequence holds: refused
+        sess.append(0, put(tags[:, :20].copy()), k[:, :20].contiguous(), k[:, :20].contiguous(), keep_all=keep_all)
+        sess.append(0, put(tags[:, 20:].copy()), k[:, 20:].contiguous(), k[:, 20:].contiguous(), keep_all=keep_all)
+        assert sess.stats(batch=1)[0].device_flags == pask.PASK_FLAG_SEQ_CAPACITY
+
+
 @pytest.mark.parametrize("pages", [3, 64, 1100])
 def test_pool_runs_out_inside_a_chunk(pages):
     """20,000 HIGH tokens of one sequence and room for `pages` pages: the first
