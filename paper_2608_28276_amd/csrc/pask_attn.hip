@@ -195,7 +195,8 @@ __device__ __forceinline__ uint32_t vcodes_pair(uint32_t n4) {
 // column = query head n), so lane (q, n) holds p of head n for slots
 // 4q..4q+3: the A operand of the p.v MFMA as it stands, with no transpose.
 // The output tile has row = query head 4q + r and column = dim 16m + n.
-template <int D, int G>
+// kFine: the weights of LOW values keep 22 bits instead of 11 (page_values).
+template <int D, int G, bool kFine>
 struct AttnState {
   uint32_t qa[4 * PageLayout<D>::NG];   // QK B operands: q of head n, dims 32i + 8q + 0..7
   f32x4_t acc[PageLayout<D>::NM];        // unnormalised outputs
@@ -238,8 +239,8 @@ __device__ __forceinline__ void row_words(uint32_t x, uint32_t (&w)[KW]) {
 
 // Scores of one page in log2 units (-inf for slots past nvalid when kMasked):
 // lane (q, n) gets head n at slots 4q..4q+3.
-template <int D, int G, bool kIsHi, bool kMasked, typename Raw>
-__device__ __forceinline__ f32x4_t page_scores(const Raw& x, const AttnState<D, G>& st, int nvalid,
+template <int D, int G, bool kIsHi, bool kMasked, typename Raw, bool kFine>
+__device__ __forceinline__ f32x4_t page_scores(const Raw& x, const AttnState<D, G, kFine>& st, int nvalid,
                                                float scale_log2, int q) {
   using PL = PageLayout<D>;
   f32x4_t sc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -276,8 +277,8 @@ __device__ __forceinline__ f32x4_t page_scores(const Raw& x, const AttnState<D, 
 
 // Online softmax for head n given the lane's max of new scores: rescale the
 // outputs and the sum only when some head's max grew.
-template <int D, int G>
-__device__ __forceinline__ void softmax_step(AttnState<D, G>& st, float mx, int q) {
+template <int D, int G, bool kFine>
+__device__ __forceinline__ void softmax_step(AttnState<D, G, kFine>& st, float mx, int q) {
   using PL = PageLayout<D>;
   const float mn = fmaxf(st.m, head_max(mx));
   if (__ballot(mn > st.m)) {
@@ -303,9 +304,26 @@ __device__ __forceinline__ uint32_t mix_pair(float p0, float p1, uint32_t s0, ui
   return __builtin_bit_cast(uint32_t, r);
 }
 
+// What mix_pair's rounding left of the same two products (r: its result), as
+// an fp16 pair scaled by 2^11 so that it keeps its bits beside any weight.
+constexpr float kRestScale = 2048.0f;
+template <int H>
+__device__ __forceinline__ uint32_t mix_rest(float p0, float p1, uint32_t s0, uint32_t s1, uint32_t r) {
+  const float a = half_bits_to_float(s0 >> (16 * H)), b = half_bits_to_float(s1 >> (16 * H));
+  const f16x2_t h = __builtin_bit_cast(f16x2_t, r);
+  const f16x2_t d = {(_Float16)(kRestScale * __builtin_fmaf(p0, a, -(float)h[0])),
+                     (_Float16)(kRestScale * __builtin_fmaf(p1, b, -(float)h[1]))};
+  return __builtin_bit_cast(uint32_t, d);
+}
+// V codes (an fp16 pair) times 2^-11: exact.
+__device__ __forceinline__ uint32_t codes_rest(uint32_t c) {
+  const f16x2_t s = {(_Float16)(1.0f / kRestScale), (_Float16)(1.0f / kRestScale)};
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2_t, c) * s);
+}
+
 // Weights p = exp2(score - max) of one page (summed into l) and O += P V.
-template <int D, int G, bool kIsHi, bool kMasked, typename Raw>
-__device__ __forceinline__ void page_values(const Raw& x, AttnState<D, G>& st, const f32x4_t& sc, int nvalid,
+template <int D, int G, bool kIsHi, bool kMasked, typename Raw, bool kFine>
+__device__ __forceinline__ void page_values(const Raw& x, AttnState<D, G, kFine>& st, const f32x4_t& sc, int nvalid,
                                             int q) {
   using PL = PageLayout<D>;
   // exp2 on v_exp_f32 directly: arguments are <= 0, and results that would
@@ -334,7 +352,12 @@ __device__ __forceinline__ void page_values(const Raw& x, AttnState<D, G>& st, c
     // V: the weights p x (V scale of the slot's group), rounded once to
     // fp16 (11 significant bits), times the exact fp16 codes on the fp16
     // MFMA.  Slots past the end get scale 0, so weight 0 (their scales are
-    // not written); their codes are finite by construction.
+    // not written); their codes are finite by construction.  kFine (the
+    // distortion, whose outputs stay fp32): a second product adds what the
+    // rounding left, as HIGH pages' split weights do.  With the 11 bits alone an
+    // int4 intervention's distance depends on the split: in a short piece the
+    // heaviest LOW weight often is the maximum, 1 and exact, in a long one a
+    // HIGH entry's weight is and every LOW weight is rounded.
     uint32_t vs[2 * PL::NG];                        // the row's V scale words: slot 4q + jj at jj*NG/2..
     row_words<2 * PL::NG, 2 * PL::NG>(x.sc, vs);
     if constexpr (kMasked) {
@@ -353,12 +376,25 @@ __device__ __forceinline__ void page_values(const Raw& x, AttnState<D, G>& st, c
       const uint32_t whi = (i & 1) ? mix_pair<1>(pr[2], pr[3], vs[PL::NG + w0], vs[3 * PL::NG / 2 + w0])
                                    : mix_pair<0>(pr[2], pr[3], vs[PL::NG + w0], vs[3 * PL::NG / 2 + w0]);
       const f16x4_t wa = __builtin_bit_cast(f16x4_t, make_uint2(wlo, whi));
+      f16x4_t wr{};
+      if constexpr (kFine) {
+        const uint32_t rlo = (i & 1) ? mix_rest<1>(pr[0], pr[1], vs[w0], vs[PL::NG / 2 + w0], wlo)
+                                     : mix_rest<0>(pr[0], pr[1], vs[w0], vs[PL::NG / 2 + w0], wlo);
+        const uint32_t rhi = (i & 1) ? mix_rest<1>(pr[2], pr[3], vs[PL::NG + w0], vs[3 * PL::NG / 2 + w0], whi)
+                                     : mix_rest<0>(pr[2], pr[3], vs[PL::NG + w0], vs[3 * PL::NG / 2 + w0], whi);
+        wr = __builtin_bit_cast(f16x4_t, make_uint2(rlo, rhi));
+      }
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         // byte jj of vc[i]: slot 4q + jj, dim 32i + n (low nibble) and 32i + 16 + n (high)
         const uint32_t n4 = (hh ? x.vc[i] >> 4 : x.vc[i]) & 0x0F0F0F0Fu;
-        const f16x4_t vb = __builtin_bit_cast(f16x4_t, make_uint2(vcodes_pair<0, 1>(n4), vcodes_pair<2, 3>(n4)));
+        const uint32_t c01 = vcodes_pair<0, 1>(n4), c23 = vcodes_pair<2, 3>(n4);
+        const f16x4_t vb = __builtin_bit_cast(f16x4_t, make_uint2(c01, c23));
         st.acc[2 * i + hh] = __builtin_amdgcn_mfma_f32_16x16x16f16(wa, vb, st.acc[2 * i + hh], 0, 0, 0);
+        if constexpr (kFine) {
+          const f16x4_t vr = __builtin_bit_cast(f16x4_t, make_uint2(codes_rest(c01), codes_rest(c23)));
+          st.acc[2 * i + hh] = __builtin_amdgcn_mfma_f32_16x16x16f16(wr, vr, st.acc[2 * i + hh], 0, 0, 0);
+        }
       }
     }
   }
@@ -367,8 +403,8 @@ __device__ __forceinline__ void page_values(const Raw& x, AttnState<D, G>& st, c
 __device__ __forceinline__ float max4(const f32x4_t& v) { return fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])); }
 
 // One page of HIGH (kIsHi) or LOW slots; kMasked when fewer than 16 are valid.
-template <int D, int G, bool kIsHi, bool kMasked, typename Raw>
-__device__ __forceinline__ void attend_page(const Raw& x, AttnState<D, G>& st, int nvalid, float scale_log2, int q) {
+template <int D, int G, bool kIsHi, bool kMasked, typename Raw, bool kFine>
+__device__ __forceinline__ void attend_page(const Raw& x, AttnState<D, G, kFine>& st, int nvalid, float scale_log2, int q) {
   const f32x4_t sc = page_scores<D, G, kIsHi, kMasked>(x, st, nvalid, scale_log2, q);
   softmax_step(st, max4(sc), q);
   page_values<D, G, kIsHi, kMasked>(x, st, sc, nvalid, q);
@@ -376,8 +412,8 @@ __device__ __forceinline__ void attend_page(const Raw& x, AttnState<D, G>& st, i
 
 // Two pages under one softmax step (one max reduction and at most one
 // rescale for both): page a is full, page b holds nvb valid slots.
-template <int D, int G, bool kIsHi, bool kMaskedB, typename Raw>
-__device__ __forceinline__ void attend_pair(const Raw& xa, const Raw& xb, AttnState<D, G>& st, int nvb,
+template <int D, int G, bool kIsHi, bool kMaskedB, typename Raw, bool kFine>
+__device__ __forceinline__ void attend_pair(const Raw& xa, const Raw& xb, AttnState<D, G, kFine>& st, int nvb,
                                             float scale_log2, int q) {
   const f32x4_t sa = page_scores<D, G, kIsHi, false>(xa, st, kPage, scale_log2, q);
   const f32x4_t sb = page_scores<D, G, kIsHi, kMaskedB>(xb, st, nvb, scale_log2, q);
@@ -681,10 +717,10 @@ constexpr int kIdChunk = 128;
 struct NoPrologue {
   __device__ __forceinline__ void operator()() const {}
 };
-template <int D, int G, bool kIsHi, bool kWindow = false, typename Prologue = NoPrologue>
+template <int D, int G, bool kIsHi, bool kWindow = false, typename Prologue = NoPrologue, bool kFine>
 __device__ __forceinline__ void run_pages(const uint8_t* pool, size_t page_bytes, int head_bytes, int n_heads,
                                           const int32_t* bt, int id0, int p0, int p1, int n_slots, int g,
-                                          AttnState<D, G>& st, float scale_log2, int q, int n,
+                                          AttnState<D, G, kFine>& st, float scale_log2, int q, int n,
                                           Prologue prologue = Prologue()) {
   using Raw = typename std::conditional<kIsHi, HiRaw<D>, LoRaw<D>>::type;
   const int lane = threadIdx.x & 63;
@@ -858,8 +894,8 @@ __device__ __forceinline__ void prepare_entry(const AttnArgs& a, int b, int g, c
 // The entry attended as a page holding just that slot (slot 0): HIGH from
 // its bf16 rows, LOW from the operands prepare_entry made; `offsets`
 // computes the LOW code offsets of q.
-template <int D, int G, typename Offsets>
-__device__ __forceinline__ void attend_entry(const AttnArgs& a, const EntryRecord& r, AttnState<D, G>& st, int q,
+template <int D, int G, bool kFine, typename Offsets>
+__device__ __forceinline__ void attend_entry(const AttnArgs& a, const EntryRecord& r, AttnState<D, G, kFine>& st, int q,
                                              int n, Offsets offsets, const LoRaw<D>& xl, const EntryRows<D>& rows) {
   using PL = PageLayout<D>;
   if ((r.word & 3) == kHigh) {
@@ -914,7 +950,7 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int slot, int 
     for (int k = 0; k < EntryRows<D>::kW; ++k) rows.w[k] = src[l * EntryRows<D>::kW + k];
   }
   const size_t bh0 = (size_t)b * a.n_q_heads + (size_t)g * G;
-  AttnState<D, G> st;
+  AttnState<D, G, !kEntries> st;                   // the distortion's calls persist nothing
   // Columns n >= G repeat head G-1 (finite scores; their results are unused).
   const uint16_t* qh = a.q + (bh0 + min(n, G - 1)) * D + 8 * q;
 #pragma unroll
