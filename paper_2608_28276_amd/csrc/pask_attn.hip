@@ -636,13 +636,11 @@ __device__ __forceinline__ int lane_len(const AttnArgs& a, const CallCounts& f, 
 // The work split of a call (pask_plan.h) from its counts: every wave of the
 // attention kernel computes the same plan; the worker that attends a segment's
 // last page leaves the segment's number of pieces for the merge.
-constexpr int kWpb = PASK_ATTN_WPB;   // workers (waves) per workgroup of the weighted attention kernel
-using WeightedPlan = StreamPlan<kWpb>;
+constexpr int kWpb = PASK_ATTN_WPB;   // workers (waves) per workgroup of calls with more segments
 constexpr int kMinPagesPerBlock = kUnitTokens / kPage;   // 8 pages: the workspace's piece size
 // Calls with few segments: pieces of at least 4 pages (8 and 12 measured slower
 // at one Qwen3-4B-shaped sequence of 2.3k entries, 2 slower too).
 constexpr int kSmallMinPages = 4;
-static_assert(PASK_ODD_WEIGHT >= 1 && PASK_ODD_WEIGHT <= 16, "odd-XCD worker weight out of range");
 
 // The units of the whole call (one KV head), those of LOW pages among them, its
 // longest sequence's units, and the units of chunk `lane` and the lower ones.
@@ -1014,17 +1012,17 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int slot, int 
   if (q == 0 && n < G4) *reinterpret_cast<float2*>(a.ws_ml + (blk * G4 + n) * 2) = make_float2(st.m, l_n);
 }
 
-// kWeighted: workgroups of kWpb worker waves, ranges over the whole list
+// kRanges: workgroups of kWpb worker waves, ranges over the whole list
 // (StreamPlan); else one single-wave workgroup per piece of a segment
 // (small_piece).  kEntries: the call may persist its step's entries.  wg:
 // the workgroup's index among the call's.
-template <int D, int G, bool kWeighted, bool kEntries>
+template <int D, int G, bool kRanges, bool kEntries>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, int wg) {
-  constexpr int kWaves = kWeighted ? kWpb : 1;   // workers per workgroup
+  constexpr int kWaves = kRanges ? kWpb : 1;   // workers per workgroup
   const int lane = threadIdx.x & 63;
   const int q = lane >> 4, n = lane & 15;
   const int H = a.cv.n_kv_heads;
-  constexpr int kSeq = kWeighted ? kFusedMaxBatch : 64;   // calls with few segments hold at most 64 sequences
+  constexpr int kSeq = kRanges ? kFusedMaxBatch : 64;   // calls with few segments hold at most 64 sequences
   __shared__ uint8_t s_tab[kWaves][128];           // Lambda's column, a copy per wave (no barrier)
   __shared__ EntryRecord s_ent[kSeq];
   __shared__ int4 s_cnt[kSeq];
@@ -1047,7 +1045,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int wg) {
       rec[1] = fused ? make_int4(r.word, r.slot, r.page, r.pos) : make_int4(0, 0, 0, 0);
     }
   }
-  if constexpr (!kWeighted) {                      // few segments: worker wg takes one piece of one
+  if constexpr (!kRanges) {                      // few segments: worker wg takes one piece of one
     const int total = __builtin_amdgcn_readlane(f.lane_incl, 63);
     const int total_lo = __builtin_amdgcn_readlane(wave_inclusive_scan(f.lane_lo), 63);
     const int u =
@@ -1071,8 +1069,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int wg) {
     const int active = cdiv(workers, a.attn_blocks / kWpb);
     if (wv >= active) return;
     const int w = uni(wg * active + wv);
-    const WeightedPlan plan =
-        stream_plan_of<kWpb>((long long)total * H, mx, a.splits, a.min_pages, workers, PASK_ODD_WEIGHT);
+    const StreamPlan plan = stream_plan_of((long long)total * H, mx, a.splits, a.min_pages, workers);
     const long long start = plan.start_of(w);
     if (start >= plan.total) return;
     const long long end = plan.end_of(w);
@@ -1103,9 +1100,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int wg) {
   }
 }
 
-template <int D, int G, bool kWeighted>
-__global__ __launch_bounds__(64 * (kWeighted ? kWpb : 1), 2) void attn_kernel(AttnArgs a) {
-  attn_body<D, G, kWeighted, true>(a, (int)blockIdx.x);
+template <int D, int G, bool kRanges>
+__global__ __launch_bounds__(64 * (kRanges ? kWpb : 1), 2) void attn_kernel(AttnArgs a) {
+  attn_body<D, G, kRanges, true>(a, (int)blockIdx.x);
 }
 
 // Online merge of the partials of one (sequence, KV head) by thread t of a
@@ -1450,16 +1447,16 @@ hipError_t scratch_workspace(void** ptr) {
 // Stream-K workers of attn_kernel<D, G> on the current device: as many waves
 // as can be resident at once (occupancy x compute units), so every worker
 // starts at launch.  Queried once per device and instance.
-template <int D, int G, bool kWeighted>
+template <int D, int G, bool kRanges>
 int attn_grid() {
-  constexpr int kWaves = kWeighted ? kWpb : 1;
+  constexpr int kWaves = kRanges ? kWpb : 1;
   constexpr int kMaxDevices = 64;
   static int cached[kMaxDevices] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
   if (cached[dev] == 0) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_kernel<D, G, kWeighted>, 64 * kWaves, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_kernel<D, G, kRanges>, 64 * kWaves, 0) !=
             hipSuccess ||
         per_cu <= 0)
       return 0;

@@ -17,18 +17,10 @@ enum Counter { kCntHi = 0, kCntLo = 1, kCntPos = 2, kCntDrop = 3, kCntForced = 4
 constexpr int kCounterStride = 8;
 constexpr int kPage = 16;          // tokens per page
 constexpr int kQGroup = 32;        // elements per fp16 scale of a RETAIN-LOW vector
-// Range an attention worker on an odd-numbered XCD takes, in sixteenths of
-// an even-XCD worker's (calls with more than kAlignedSegments segments).
-// Equal ranges: with 512 workers streaming (stream_workers) 15 measured 4%
-// slower at batch 64 (195.0 against 188.0 us), and with all 2,048 5% slower on
-// an int4-heavy history (112.7 against 107.2 us).
-#ifndef PASK_ODD_WEIGHT
-#define PASK_ODD_WEIGHT 16
-#endif
 // Stream-K workers (single waves) per workgroup of the attention kernel for
-// those calls: 2,048 single-wave workgroups took 4.5 us to dispatch; two waves
-// per workgroup measured as four on HIGH pages and 5% slower on LOW pages
-// (112.7 against 107.2 us at 87% LOW).
+// calls with more than kAlignedSegments segments: 2,048 single-wave workgroups
+// took 4.5 us to dispatch; two waves per workgroup measured as four on HIGH
+// pages and 5% slower on LOW pages (112.7 against 107.2 us at 87% LOW).
 #ifndef PASK_ATTN_WPB
 #define PASK_ATTN_WPB 4
 #endif

@@ -63,78 +63,44 @@ __host__ __device__ __forceinline__ SeqPages make_pages(int n_hi, int n_win, int
 }
 // Units of a LOW store of n_lo slots.
 __host__ __device__ __forceinline__ int low_len_of(int n_lo) { return kUnit * cdiv(n_lo, 16); }
-// Unit offset of page j inside its segment.
-__host__ __device__ __forceinline__ int page_start(const SeqPages&, int j) { return kUnit * j; }
-// First page whose unit offset is >= u (s.np when there is none).
+// First page whose unit offset, kUnit per page, is >= u (s.np when there is none).
 __host__ __device__ __forceinline__ int first_page_at(const SeqPages& s, int u) {
   const int j = cdiv(u, kUnit);
   return j < s.np ? j : s.np;
 }
 
-// Calls with many (sequence, KV head) segments.  The work list is
-// the segments (sequence b, KV head g) in that nesting order, each the units
-// of its pages.  Worker w (a wave; kWpb of them per workgroup) takes the
-// pages that start in its contiguous range [start_of(w), end_of(w)), of
-// weight(w) x step units.  Workgroups are dealt to the 8 XCDs in turn; a worker
-// on an odd-numbered one weighs `odd` sixteenths against 16 on an even one
-// (PASK_ODD_WEIGHT: equal; equal also when the ranges are at their minimum
-// size, a latency-bound call).
-// Every range is at least lo units, at least one page (pages start at
-// multiples of kUnit), so each range between the first and the last of a
-// segment holds a page of it, and no segment is cut into more than `splits`
-// pieces (lo >= mx / (splits - 1)).
-template <int kWpb>
+// Calls with many (sequence, KV head) segments.  The work list is the
+// segments (sequence b, KV head g) in that nesting order, each the units of
+// its pages.  Worker w (a wave) takes the pages that start in the w-th of equal
+// contiguous ranges, [start_of(w), end_of(w)).  Every range is a multiple of
+// half a page, at least min_pages pages and lo units, at least one page (pages
+// start at multiples of kUnit), so each range between the first and the last of
+// a segment holds a page of it, and no segment is cut into more than `splits`
+// pieces (lo >= mx / (splits - 1)).  Workgroups are dealt to the 8 XCDs in
+// turn; ranges 15/16 as long on the odd-numbered ones measured 4% slower at
+// batch 64 with 512 workers streaming (195.0 against 188.0 us) and 5% slower
+// with all 2,048 on an int4-heavy history (112.7 against 107.2 us).
 struct StreamPlan {
   long long total;   // units
-  int step;          // units per sixteenth of weight
-  int odd;           // weight of a worker on an odd XCD, in sixteenths
-  __host__ __device__ __forceinline__ int octet() const { return kWpb * (4 * 16 + 4 * odd); }   // 8 workgroups
-  __host__ __device__ __forceinline__ int weight(int w) const { return ((w / kWpb) & 1) ? odd : 16; }
-  // Sixteenths of weight of workers 0..w-1.
-  __host__ __device__ __forceinline__ long long weight_before(int w) const {
-    const int wg = w / kWpb, j = wg & 7;
-    return (long long)(wg >> 3) * octet() + kWpb * ((j + 1) / 2 * 16 + (j / 2) * odd) + (w % kWpb) * weight(w);
-  }
-  __host__ __device__ __forceinline__ long long start_of(int w) const {
-    return odd == 16 ? (long long)w * (16 * step) : weight_before(w) * step;
-  }
+  int units;         // of a range
+  __host__ __device__ __forceinline__ long long start_of(int w) const { return (long long)w * units; }
   __host__ __device__ __forceinline__ long long end_of(int w) const {
-    const long long e = start_of(w) + (long long)weight(w) * step;
+    const long long e = start_of(w) + units;
     return e < total ? e : total;
   }
   // Worker whose range holds unit u.
-  __host__ __device__ __forceinline__ long long block_of(long long u) const {
-    if (odd == 16) return udiv(u, 16LL * step);
-    const long long wu = udiv(u, step);            // sixteenths of weight before u
-    const long long o = udiv(wu, octet());
-    int r = (int)(wu - o * octet()), j = 0;
-    while (r >= kWpb * weight(j * kWpb)) {
-      r -= kWpb * weight(j * kWpb);
-      ++j;
-    }
-    return o * 8 * kWpb + j * kWpb + r / weight(j * kWpb);
-  }
+  __host__ __device__ __forceinline__ long long block_of(long long u) const { return udiv(u, units); }
 };
 
 // total: units of the call; mx: units of its longest segment; splits: pieces
 // the workspace holds per segment (>= 2); min_pages: the fewest pages a range
-// takes; n: workers; odd: the odd-XCD weight in sixteenths (1..16).
-template <int kWpb>
-__host__ __device__ __forceinline__ StreamPlan<kWpb> stream_plan_of(long long total, int mx, int splits,
-                                                                    int min_pages, int n, int odd) {
-  StreamPlan<kWpb> p;
-  p.total = total;
+// takes; n: workers.
+__host__ __device__ __forceinline__ StreamPlan stream_plan_of(long long total, int mx, int splits, int min_pages,
+                                                              int n) {
   const long long lo0 = (long long)kUnit * min_pages, lo1 = cdiv(mx, splits - 1);
-  const long long lo = lo0 > lo1 ? lo0 : lo1;
-  p.odd = odd;
-  long long step = udiv(total + p.weight_before(n) - 1, p.weight_before(n));
-  if (step * odd < lo) {                           // ranges at their minimum: equal ones
-    p.odd = 16;
-    const long long even = udiv(total + p.weight_before(n) - 1, p.weight_before(n));
-    step = even > (lo + 15) / 16 ? even : (lo + 15) / 16;
-  }
-  p.step = (int)(step < 0x7FFFFFFF / 16 ? step : 0x7FFFFFFF / 16);
-  return p;
+  const long long least = ((lo0 > lo1 ? lo0 : lo1) + 15) / 16, even = udiv(total + 16LL * n - 1, 16LL * n);
+  const long long halves = even > least ? even : least;
+  return StreamPlan{total, 16 * (int)(halves < 0x7FFFFFFF / 16 ? halves : 0x7FFFFFFF / 16)};
 }
 
 // Workers such a call uses of the `limit` resident ones (`share` calls run on
@@ -153,30 +119,6 @@ __host__ __device__ __forceinline__ int stream_workers(int total, int total_lo, 
   if (total_lo >= total / 6 || total / kUnit < 64 * batch) return limit;
   const int few = 512 * 128 / head_dim / share;
   return few < limit ? few : limit;
-}
-
-// Equal ranges of U units.  Calls with few segments split every segment so, by
-// itself, with unit 0 at its first page (small_piece).
-struct EvenPlan {
-  long long total;   // units
-  int U;             // units per worker
-  __host__ __device__ __forceinline__ long long start_of(int w) const { return (long long)w * U; }
-  __host__ __device__ __forceinline__ long long end_of(int w) const {
-    const long long e = (long long)(w + 1) * U;
-    return e < total ? e : total;
-  }
-  __host__ __device__ __forceinline__ long long block_of(long long u) const { return udiv(u, U); }
-};
-__host__ __device__ __forceinline__ EvenPlan even_plan_of(long long total, int mx, int splits, int min_pages, int n) {
-  EvenPlan p;
-  p.total = total;
-  const long long even = udiv(total + n - 1, n);
-  int U = kUnit * min_pages;
-  if (even > U) U = (int)(even < 0x7FFFFFFF ? even : 0x7FFFFFFF);
-  const int lo1 = cdiv(mx, splits - 1);
-  if (lo1 > U) U = lo1;
-  p.U = U;
-  return p;
 }
 
 // Calls with at most kAlignedSegments segments: every segment is cut by itself
@@ -221,16 +163,11 @@ __host__ __device__ __forceinline__ void small_piece(const SeqPages& s, int n, i
     j1 = s.np;
     return;
   }
-  const EvenPlan e = even_plan_of(kUnit * s.np_l, kUnit * s.np_l, n + 1, 1, n);
-  const int a = first_page_at(s, (int)e.start_of(p)), b = first_page_at(s, (int)e.end_of(p));
+  const int len = kUnit * s.np_l, units = (int)udiv((long long)len + n - 1, n);
+  const long long u0 = (long long)p * units, u1 = u0 + units;
+  const int a = first_page_at(s, (int)(u0 < len ? u0 : len)), b = first_page_at(s, (int)(u1 < len ? u1 : len));
   j0 = a < s.np_l ? a : s.np_l;
   j1 = b < s.np_l ? b : s.np_l;
-}
-
-// Pieces of the segment starting at unit seg0 with pages sp (sp.np > 0).
-template <typename Plan>
-__host__ __device__ __forceinline__ int n_pieces(const Plan& plan, const SeqPages& sp, long long seg0) {
-  return (int)(plan.block_of(seg0 + page_start(sp, sp.np - 1)) - plan.block_of(seg0)) + 1;
 }
 
 }  // namespace pask

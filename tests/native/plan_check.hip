@@ -1,17 +1,20 @@
-// The attention call's work split (pask_plan.h), checked on the CPU over
-// random calls: sequences with random HIGH / window / LOW page counts (empty
-// ones included), 1-8 KV heads, the workspace's piece bound of the C ABI for
-// a hint at the longest sequence, and worker counts from 1 to 4096.  For the
-// per-XCD weighted plan (calls with more than 64 segments; odd-XCD weights
-// 12..16, four worker waves per workgroup or one) and the equal plan (at most
-// 64), every worker's range is walked the way the attention kernel walks it,
-// and:
+// The attention's split of the whole work list (pask_plan.h), checked on the
+// CPU over random calls: sequences with random HIGH / window / LOW page counts
+// (empty ones included), 1-8 KV heads, head_dim 64 and 128, the workspace's
+// piece bound of the C ABI for a hint at the longest sequence or one as low as
+// two, and launches of 1 to 1,024 workgroups of four waves, for a decode call and for one of the
+// distortion's two caches (which takes this split at any number of segments).
+// The workers are as many as stream_workers says, numbered as the attention
+// kernel numbers the first waves of every workgroup; each one's range is
+// walked the way the kernel walks it, and:
 //   - the ranges tile [0, total): every page is attended exactly once;
 //   - the ranges tile [0, total) in worker order and block_of(u) is the
 //     worker whose range holds u, for every page start u;
 //   - every piece a worker writes has index w - block_of(seg0) in
 //     [0, n_pieces) and n_pieces <= splits, and every index in [0, n_pieces)
-//     of every segment is written once (the merge reads exactly these).
+//     of every segment is written once, the last by the worker that holds the
+//     segment's last page (whose index + 1 is the merge's piece count).
+// Both kinds of call, all workers and few, must have come up often.
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -47,8 +50,12 @@ struct Call {
   int mx;
 };
 
-template <typename Plan>
-int check(const Call& c, const Plan& plan, int n_workers_all, int splits, const char* what) {
+// Pieces of the segment starting at unit seg0 with pages sp (sp.np > 0).
+int n_pieces(const StreamPlan& plan, const SeqPages& sp, long long seg0) {
+  return (int)(plan.block_of(seg0 + kUnit * (sp.np - 1)) - plan.block_of(seg0)) + 1;
+}
+
+int check(const Call& c, const StreamPlan& plan, const std::vector<int>& workers, int splits, const char* what) {
   // pieces[seg] -> which indices were written
   const int B = (int)c.seqs.size(), H = c.H;
   std::vector<std::vector<int>> written(B * H);
@@ -59,7 +66,7 @@ int check(const Call& c, const Plan& plan, int n_workers_all, int splits, const 
   std::vector<long long> page_base(B * H + 1, 0);
   for (int b = 0; b < B; ++b)
     for (int g = 0; g < H; ++g) page_base[b * H + g + 1] = page_base[b * H + g] + c.seqs[b].np;
-  for (int w = 0; w < n_workers_all; ++w) {
+  for (int w : workers) {
     const long long start = plan.start_of(w), end = plan.end_of(w);
     if (start >= end) continue;
     if (plan.block_of(start) != w) { printf("%s: block_of(start_of(%d)) = %lld\n", what, w, plan.block_of(start)); return 1; }
@@ -84,10 +91,11 @@ int check(const Call& c, const Plan& plan, int n_workers_all, int splits, const 
           return 1;
         }
         written[b * H + g].push_back((int)slot);
+        if (j1 == sp.np && slot != np - 1) { printf("%s: last page in piece %lld of %d\n", what, slot, np); return 1; }
         for (int j = j0; j < j1; ++j) {
           const long long pg = page_base[b * H + g] + j;
           if (seen[pg]++) { printf("%s: page attended twice\n", what); return 1; }
-          if (plan.block_of(seg0 + page_start(sp, j)) != w) { printf("%s: block_of(page) != worker\n", what); return 1; }
+          if (plan.block_of(seg0 + kUnit * j) != w) { printf("%s: block_of(page) != worker\n", what); return 1; }
         }
       }
       if (j1 < sp.np) break;
@@ -122,21 +130,23 @@ int check(const Call& c, const Plan& plan, int n_workers_all, int splits, const 
 int main(int argc, char** argv) {
   const int rounds = argc > 1 ? atoi(argv[1]) : 400;
   int bad = 0;
-  long long calls = 0;
+  long long calls = 0, few = 0;
   for (int r = 0; r < rounds && !bad; ++r) {
     Call c;
     const int kind = rnd(4);
     const int B = kind == 0 ? 1 + rnd(8) : (kind == 1 ? 1 + rnd(64) : 1 + rnd(300));
     c.H = 1 + rnd(8);
     int mx_tok = 0;
-    long long acc = 0;
+    const bool distortion = rnd(3) == 0;             // persists nothing
+    long long acc = 0, acc_lo = 0;
     for (int b = 0; b < B; ++b) {
       const int shape = rnd(6);
       int hi = shape == 0 ? 0 : rnd(shape == 1 ? 40 : 9000), win = rnd(3) ? 0 : rnd(70), lo = rnd(2) ? rnd(3000) : 0;
       if (shape == 5) hi = 20000 + rnd(20000);
-      SeqPages s = make_pages(hi, win, lo, rnd(3) == 0 ? 1 : 0);   // with or without the step's own entry
+      SeqPages s = make_pages(hi, win, lo, !distortion && rnd(3) == 0 ? 1 : 0);   // with or without the step's own entry
       c.excl.push_back(acc);
       acc += s.len;
+      acc_lo += low_len_of(lo);
       c.seqs.push_back(s);
       mx_tok = std::max(mx_tok, hi + win + lo + 1);
     }
@@ -146,25 +156,21 @@ int main(int argc, char** argv) {
     if (c.total == 0) continue;
     const long long segs = (long long)B * c.H;
     const int hint = std::max(1, mx_tok + (int)rnd(500));
-    const int splits = splits_for(hint, segs);
-    static const int workers[] = {1, 7, 64, 100, 256, 512, 1000, 2048, 2047, 4096};
-    const int n = workers[rnd(sizeof(workers) / sizeof(workers[0]))];
+    const int splits = rnd(4) ? splits_for(hint, segs) : 2 + rnd(6);   // or (a scratch limit) as few as two
+    static const int groups[] = {1, 2, 16, 25, 64, 128, 250, 511, 512, 1024};
+    const int limit = 4 * groups[rnd(sizeof(groups) / sizeof(groups[0]))], D = rnd(2) ? 64 : 128;
+    const int n = stream_workers((int)acc, (int)acc_lo, B, D, limit, distortion ? 2 : 1);
+    const int active = cdiv(n, limit / 4);
+    std::vector<int> workers;
+    for (int wg = 0; wg < limit / 4; ++wg)
+      for (int wv = 0; wv < 4 && wv < active; ++wv) workers.push_back(wg * active + wv);
     ++calls;
-    if (segs > 64) {
-      const int n4 = (n + 3) / 4 * 4;                // whole workgroups of four worker waves
-      for (int odd = 12; odd <= 16 && !bad; ++odd) {
-        const StreamPlan<4> p4 = stream_plan_of<4>(c.total, c.mx, splits, 8, n4, odd);
-        bad |= check(c, p4, n4, splits, "weighted, 4 waves");
-        const StreamPlan<1> p1 = stream_plan_of<1>(c.total, c.mx, splits, 8, n, odd);
-        bad |= check(c, p1, n, splits, "weighted, 1 wave");
-      }
-    } else {
-      const EvenPlan p = even_plan_of(c.total, c.mx, splits, 4, n);
-      bad |= check(c, p, (int)((c.total + p.U - 1) / p.U), splits, "even");
-      const int capped = std::min(splits, 33);     // the attention's ranges of >= 1/32 of the longest segment
-      const EvenPlan pc = even_plan_of(c.total, c.mx, capped, 4, n);
-      bad |= check(c, pc, (int)((pc.total + pc.U - 1) / pc.U), capped, "even, ranges >= 1/32 of the longest segment");
-    }
+    few += n < limit ? 1 : 0;
+    bad |= check(c, stream_plan_of(c.total, c.mx, splits, 8, n), workers, splits, distortion ? "distortion" : "decode");
+  }
+  if (!bad && (few < calls / 20 || few > calls - calls / 20)) {
+    printf("FAIL: few workers in %lld of %lld calls\n", few, calls);
+    return 1;
   }
   printf("%s: %lld calls\n", bad ? "FAIL" : "ok", calls);
   return bad;

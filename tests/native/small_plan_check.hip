@@ -25,6 +25,13 @@ static uint32_t rnd(uint32_t n) {
   return (uint32_t)(g_s % n);
 }
 
+static int splits_for(int hint, long long segments) {   // as the C ABI sizes the workspace
+  const int coarse = (hint + 127) / 128 + 2;
+  if (segments > 64) return coarse;
+  const int fine = (hint + 15) / 16 + 2;
+  return std::max(coarse, std::min(fine, (int)(4096 / std::max<long long>(segments, 1))));
+}
+
 int main(int argc, char** argv) {
   const int rounds = argc > 1 ? atoi(argv[1]) : 400;
   for (int r = 0; r < rounds; ++r) {
@@ -43,7 +50,7 @@ int main(int argc, char** argv) {
       mx_tok = std::max(mx_tok, hi + win + lo + 1);
     }
     // the C ABI's bound for a hint at the longest sequence, or (a scratch limit) as few as two
-    const int splits = rnd(4) ? (mx_tok + 127) / 128 + 2 : 2 + rnd(6);
+    const int splits = rnd(4) ? splits_for(mx_tok, (long long)B * H) : 2 + rnd(6);
     const int u = small_units(total, total_lo, mx, splits, 4, D);
     std::vector<int> cuts(B), pieces(B), upto(B);
     int acc = 0;

@@ -1,7 +1,8 @@
 """The bulk append's plan, and the plan of a decode call of many sequences, at
-the sizes where they split differently: around one token per lane and round, around a whole chunk of tokens and across chunks,
-with a recent window, with a pool that runs out inside a chunk, and with the
-online controller near its reserves.  Decisions, slots, counters, lists and
+the sizes where they split differently: around one token per lane and round,
+around a whole chunk of tokens and across chunks, with a recent window, with a
+pool that runs out inside a chunk, and with the online controller near its
+reserves.  Decisions, slots, counters, lists and
 budgets against the CPU oracle, all exact."""
 
 import numpy as np
@@ -205,13 +206,31 @@ def test_decode_call_of_many_sequences(B):
 @pytest.mark.parametrize("B,Hkv,D", [(16, 8, 128), (17, 8, 128), (18, 7, 64), (64, 2, 64), (64, 3, 64)])
 def test_decode_call_around_few_segments(B, Hkv, D):
     """128 (sequence, KV head) segments and fewer are cut one by one, more as
-    ranges over the whole list, whose workers are few when the history is long
-    and HIGH: lengths from 0 to 70 pages, so that segments have one to several
-    pieces, and one sequence of 1,900 tokens; both stores; two steps."""
+    ranges over the whole list, here by every worker (short histories): lengths
+    from 0 to 70 pages, so that segments have one to several pieces, and one
+    sequence of 1,900 tokens; both stores; two steps."""
     say(f"case: decode of {B} x {Hkv} segments, D={D}")
-    pol = make_policy(6, 1, 1, 0.4, seed=B + Hkv)
     P = [(97 * b) % 1100 for b in range(B)]
     P[-1] = 1900
+    _two_steps(B, Hkv, D, P)
+
+
+@pytest.mark.parametrize("B,Hkv,D", [(17, 8, 128), (33, 4, 128), (19, 7, 64), (65, 2, 64), (130, 1, 64)])
+def test_decode_call_of_long_histories(B, Hkv, D):
+    """More than 128 segments whose history is long (64 pages a sequence and
+    more) and mostly HIGH are streamed by few workers, the first wave or two of
+    each workgroup: lengths of 1,100 to 2,900 tokens, some sequences empty or of
+    one page; both stores; two steps."""
+    say(f"case: decode of {B} x {Hkv} long segments, D={D}")
+    P = [1100 + (397 * b) % 1800 for b in range(B)]
+    P[1], P[B // 2] = 0, 9
+    counts = np.asarray(P) + 40
+    assert np.sum(counts // 16) >= 64 * B and 40 * B < counts.sum() / 6, "few workers"
+    _two_steps(B, Hkv, D, P)
+
+
+def _two_steps(B, Hkv, D, P):
+    pol = make_policy(6, 1, 1, 0.4, seed=B + Hkv)
     base = function_call_tags(B + 40, 6)
     tags = np.stack([base[b:b + 40] for b in range(B)])
     sc = Scenario(pol, B=B, L=1, Hq=2 * Hkv, Hkv=Hkv, D=D, prompt_lens=P, gen_tags=tags, seed=B)

@@ -20,5 +20,5 @@ def test_work_split_invariants(tmp_path):
                         f"{ROOT}/tests/native/plan_check.hip", "-o", str(exe)], capture_output=True, text=True,
                        timeout=300)
     assert b.returncode == 0, b.stderr[-4000:]
-    r = subprocess.run([str(exe), "600"], capture_output=True, text=True, timeout=600)
+    r = subprocess.run([str(exe), "4000"], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout[-3000:]
