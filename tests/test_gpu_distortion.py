@@ -8,7 +8,7 @@ compared with the oracle's value for that (sequence, step, layer), and the
 final D with the oracle's Eq. 4 outer loop.
 
 Tolerance: the GPU outputs are fp32 merges of split-K partials whose p.v
-weights carry >= 16 significant bits; the bound would hold for 11: each output
+weights carry >= 22 significant bits; the bound would hold for 11: each output
 element is within delta_o ~ 2^-11 |v| / sqrt(n_eff) of the fp64 one; over D
 dims the error vector has norm ||e|| <= delta = 4e-3 (generous for D <= 128),
 and ||d + e||^2 - ||d||^2 is within 2 delta ||d|| + delta^2."""
@@ -146,13 +146,14 @@ def test_distortion_of_long_histories(Hq, Hkv, D, action):
     pieces are up to 32 pages long, and the longest segment has up to 70 of them
     (the distance's rounds of eight).
 
-    Tolerance: weights carry 16 bits (HIGH, two bf16 parts) or more (LOW, two
-    fp16 parts), each off by at most 2^-17 of itself and 2^-17 / sqrt(3) in the
-    root mean square, independently, so an output of norm |o| is off by about
-    e = 2^-17 / sqrt(3) |o| in a direction of its own, each of the two outputs
+    Tolerance: weights carry 22 bits and more (three bf16 parts of a HIGH one,
+    two fp16 parts of a LOW one) and the scores, up to about 10 in log2 units,
+    are fp32 sums, so that a weight is off by about 2^-20 of itself,
+    independently of the others; an output of norm |o| then is off by about
+    e = 2^-20 |o| / sqrt(3) in a direction of its own, each of the two outputs
     by as much, and |d|^2, d their difference, by 2 |d| sqrt(2) e / sqrt(D).
-    Over the calls' root mean square, four times that (LOW weights of 11 bits,
-    32 times coarser, over 8-13% of the entries, measured 9 to 11 times)."""
+    Over the calls' root mean square, three times that (measured 0.5 to 1.1
+    times; 16 bits of a HIGH weight 2.6 to 4.4, 11 bits of a LOW one 72 to 87)."""
     from paper_2608_28276_amd import pask
     from paper_2608_28276_amd.session import PaskSession
     say(f"case: distortion of long histories, Hq {Hq} Hkv {Hkv} D {D} action {action}")
@@ -201,7 +202,7 @@ def test_distortion_of_long_histories(Hq, Hkv, D, action):
                 continue
             h = int(np.square(o[0] - o[1]).sum(-1).argmax())
             err.append(got[b] / want - 1.0)
-            expect.append(2 * np.sqrt(2) * 2.0 ** -17 / np.sqrt(3) * np.linalg.norm(o[0][h]) / np.sqrt(want * D))
+            expect.append(2 * np.sqrt(2) * 2.0 ** -20 / np.sqrt(3) * np.linalg.norm(o[0][h]) / np.sqrt(want * D))
     rms = lambda x: float(np.sqrt(np.mean(np.square(x))))
     say(f"relative error rms {rms(err):.2e} worst {np.abs(err).max():.2e}, expected rms {rms(expect):.2e}")
-    assert rms(err) <= 4 * rms(expect), (rms(err), rms(expect))
+    assert rms(err) <= 3 * rms(expect), (rms(err), rms(expect))
