@@ -12,6 +12,11 @@ import torch
 
 from . import pask
 
+# The current stream's raw handle: building torch's Stream object costs 2 us of
+# a call's 10.6.  Not in torch's public interface: a torch without it goes the
+# public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 
 class PaskSession:
     """One cache of `max_batch` sequences x `n_layers` layers on one GPU."""
@@ -50,9 +55,10 @@ class PaskSession:
 
     @property
     def stream(self) -> int:
-        # the raw handle: building torch's Stream object costs 2 us of a call's 10.6
+        if _raw_stream is None:
+            return torch.cuda.current_stream(self.device).cuda_stream
         index = self.device.index
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+        return _raw_stream(torch.cuda.current_device() if index is None else index)
 
     # -- the hot path ------------------------------------------------------
     def append(self, layer: int, tags, k, v, n_new=None, keep_all: bool = False, batch: int | None = None,

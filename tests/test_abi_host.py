@@ -396,3 +396,22 @@ def test_debug_mode_keeps_the_validation_codes():
                        cwd=ROOT, env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert p.returncode == 0, p.stdout[-3000:]
     assert re.search(r"\b3 passed\b", p.stdout), p.stdout[-1000:]
+
+
+@pytest.mark.parametrize("device", ["cuda:3", "cuda"])
+def test_session_stream_with_and_without_the_raw_handle(monkeypatch, device):
+    """The stream a session launches on is its device's current one, also where
+    torch does not have the private call that returns the handle by itself."""
+    import torch
+
+    from paper_2608_28276_amd import session
+    s = object.__new__(session.PaskSession)
+    s.device = torch.device(device)
+    index = s.device.index if s.device.index is not None else 1
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 1)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d: type("S", (), {
+        "cuda_stream": 100 + (torch.device(d).index if torch.device(d).index is not None else 1)}))
+    monkeypatch.setattr(session, "_raw_stream", lambda i: 100 + i)
+    assert s.stream == 100 + index
+    monkeypatch.setattr(session, "_raw_stream", None)
+    assert s.stream == 100 + index
