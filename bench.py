@@ -575,13 +575,15 @@ def kernel_source_digest() -> str:
 def attn_kernels(cfg, window: int = 0, controller: bool = False) -> str:
     """The kernels of one pask_decode_attn call with its step's token: calls
     with at most 128 (sequence, KV head) segments cut every segment by itself
-    and use the sliced merge, larger ones take ranges over the whole page list
-    and the merge; the one-token append kernel comes first when the call cannot
+    and use the sliced merge (4 positions a block for at most 8 segments whose
+    workspace holds 64 pieces each or more, else 16), larger ones take ranges
+    over the whole page list and the merge; the one-token append kernel comes first when the call cannot
     persist the token in those (more than 1,024 sequences, a recent window or
     parser states)."""
     D, G = cfg.head_dim, cfg.group_size
     if cfg.batch <= 64 and cfg.batch * cfg.n_kv_heads <= 128:
-        positions = 4 if cfg.batch * cfg.n_kv_heads <= 8 else 16
+        pieces = (cfg.prompt_max + cfg.gen_tokens + 15) // 16 + 2
+        positions = 4 if cfg.batch * cfg.n_kv_heads <= 8 and pieces >= 64 else 16
         k = f"attn_kernel<{D}, {G}, false> + attn_merge_sliced_kernel<{D}, {G}, {positions}>"
     else:
         k = f"attn_kernel<{D}, {G}, true> + attn_merge_kernel<{D}, {G}>"

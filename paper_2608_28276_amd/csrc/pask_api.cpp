@@ -241,8 +241,9 @@ struct WsLayout {
 
 // Partials of the attention pieces: per (sequence, KV head, piece) a block of
 // G4 = max(G, 4) query-head rows of head_dim fp32 values, and G4 (max, sum)
-// pairs; then 8 int32 per sequence for a call that persists its step's
-// entries (the counts its attention planned with and each entry's outcome).
+// pairs; then 8 int32 per sequence: 8 u16 numbers of pieces, one per KV head,
+// which every merge reads, and the outcome of the step's entry where the call
+// persists it (in a distortion call, the arrivals of the sequence's heads).
 WsLayout ws_layout(const pask_geom* g, int32_t batch, int splits) {
   WsLayout w;
   const uint64_t group = (uint64_t)std::max(4, g->n_q_heads / g->n_kv_heads);

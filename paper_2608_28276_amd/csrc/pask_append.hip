@@ -218,7 +218,7 @@ __device__ __forceinline__ void budget_fast_table(const BudgetTable& t, int grou
 // holds for good once it holds (the budget never grows), so a run ends only
 // where a state's reserve is reached.  actions[jj - jj0] gets the layer's
 // action.  The plan kernel of 384 replayed tokens of 16 sequences (two groups)
-// took 420 us with one thread taking one token after another, 30 us so.
+// took 433 us with one thread taking one token after another, 30 us so.
 __device__ __forceinline__ void budget_walk(const BudgetTable& t, const BudgetFast& f, const uint8_t* tags,
                                             const uint8_t* states, int jj0, int jj1, int pos0, int group,
                                             int64_t& R, uint32_t& flags, uint8_t* actions) {
@@ -290,9 +290,9 @@ __device__ __forceinline__ void budget_walk(const BudgetTable& t, const BudgetFa
 // vector instructions: a 256-entry table in LDS gives a tag's action, forced
 // and bad bits at once, and drops, losses and flags follow from the totals.
 // Against chunks of one token per thread, each with four exchanges (kernel
-// times): one 32,000-token labelled prompt 127.7 -> 21.9 us, 32 labelled
-// prompts of up to 16,384 tokens 68.3 -> 13.4 us, 64 kept prompts of up to
-// 8,192 tokens 31.1 -> 9.0 us.
+// times): one 32,000-token labelled prompt 123.9 -> 20.6 us, 32 labelled
+// prompts of up to 16,384 tokens 68.7 -> 14.0 us, 64 kept prompts of up to
+// 8,192 tokens 34.9 -> 10.6 us.
 //
 // kBudget: the tokens carry parser states and wave 0 walks the controller over
 // the chunk first (table in LDS).
@@ -1053,7 +1053,7 @@ __device__ __forceinline__ uint4 row_piece(const AppendArgs& a, int b, int piece
 // wait for the decision is issued at its start - the token's rows, its tag,
 // the counters, then what the position gives: the leaving entry's window slot
 // and action, and the page of either store's next slot (64 sequences with
-// W = 64: 9.5 -> 8.4 us; 16 under the controller: 6.7 -> 6.4).
+// W = 64: 9.6 -> 8.6 us; 16 under the controller: 6.5 both ways).
 template <int D, bool kWindow>
 __global__ __launch_bounds__(256) void append_step_kernel(AppendArgs a) {
   __shared__ uint8_t s_a0[64], s_amin[64];
@@ -1159,7 +1159,7 @@ __global__ __launch_bounds__(256) void append_step_kernel(AppendArgs a) {
 // The new tokens that stay in the window (the last min(n_fit, W) of the
 // call) into their window slots, a block per token; after the pack kernel has
 // read the slots they replace.  (16 tokens in turn per block left most of the
-// chip idle: 27.9 us for 64 sequences and W = 64, 17.3 so.)
+// chip idle: 29.5 us for 64 sequences and W = 64, 17.7 so.)
 template <int D>
 __global__ __launch_bounds__(256) void append_window_fill_kernel(AppendArgs a) {
   const CacheView& cv = a.cv;
@@ -1199,8 +1199,12 @@ static int pack_pages(int n) { return (n + 28) / kPage + 2; }
 // to 2 per compute unit for 64 KiB pages and 3 for 32 KiB ones: 4 have more
 // loads and stores in flight than the memory takes well (64 prompts of up to
 // 8,192 tokens, 8 KV heads, D 128: 478 us with 4, 450 with 2, 617 with 1; 4 KV
-// heads 226 with 4, 221 with 3, 236 with 2).  A labelled prompt's LOW pages
-// are bound by arithmetic and want all 4 (229 us, 252 with 3).
+// heads 226 with 4, 221 with 3, 236 with 2; short prompts gain less, 384 of up
+// to 768 tokens 268 -> 264, and 64 of them lose a little, 54.6 -> 55.5).  At
+// head_dim 64 a block holds half as many bytes and idle LDS only costs (8 KV
+// heads, the same 64 prompts: 226 us without, 229 with 4 blocks, 261 with 3).
+// A labelled prompt's LOW pages are bound by arithmetic and want all 4 (229
+// us, 252 with 3).
 static unsigned pack_idle_lds(const AppendArgs& a) {
   if (!(a.flags & kKeepAll) || a.cv.head_dim != 128 || a.cv.n_kv_heads < 4) return 0;
   constexpr unsigned kBlock = kPage * (8 * 128 * 2 + kLdsRowPad) + kPage * 4, kCu = 160 << 10;

@@ -1345,7 +1345,7 @@ __global__ __launch_bounds__(64) void attn_merge_sliced_kernel(AttnArgs a) {
 // The attention of the distortion's two caches as one launch, half of the
 // workgroups (hence of the workers) each: two launches in turn each paid the
 // launch, the plan and a tail of their own (16 sequences, prompts of
-// 1,024-4,096 tokens, 8 KV heads, D 128: 2 x 37.3 us; one launch 67.2 us).
+// 1,024-4,096 tokens, 8 KV heads, D 128: 2 x 38.0 us; one launch 65.4 us).
 template <int D, int G>
 __global__ __launch_bounds__(64 * kWpb, 2) void attn_pair_kernel(AttnArgs ref, AttnArgs itv) {
   const int half = (int)gridDim.x / 2;
@@ -1375,7 +1375,7 @@ __device__ __forceinline__ float wave_sum_f(float x) {
 // query heads (Eq. 4, inside the expectation) to dist[b].  Nothing is done for
 // a sequence with in_s[b] == 0 (in_s null: every sequence counts).  One block
 // per sequence, eight KV heads at a time, left all but B compute units idle:
-// 50.4 us at 16 sequences of up to 4,608 entries, 13.6 us so.
+// 50.2 us at 16 sequences of up to 4,608 entries, 9.0 us so.
 template <int D, int G>
 __global__ __launch_bounds__(256) void distortion_kernel(AttnArgs ref, AttnArgs itv, const uint8_t* in_s,
                                                          float* dist) {

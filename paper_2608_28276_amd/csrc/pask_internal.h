@@ -103,12 +103,12 @@ struct AttnArgs {
   const uint8_t* tags_new;  // [batch]
   const uint16_t* k_new;    // bf16 bits [batch][Hkv][D]
   const uint16_t* v_new;
-  int32_t* ws_seq;          // [batch][8]: 8 u16 piece counts (one per KV head), then the entry's outcome
+  int32_t* ws_seq;          // [batch][8]: 8 u16 piece counts (one per KV head), then the entry's outcome (distortion: arrivals)
   TableColumn tab;          // Lambda's column of the layer (with tags_new)
   float scale_log2;         // softmax_scale * log2(e)
   int32_t layer, batch, n_q_heads, splits;   // splits: partials per (b, g) the workspace holds
   int32_t attn_blocks;      // stream-K workers (waves) of the attention kernel, set at launch
-  int32_t min_pages;        // fewest pages a worker takes (HIGH-page weight), set at launch
+  int32_t min_pages;        // fewest pages a worker takes, set at launch
 };
 
 // The workspace of calls with at most kSmallSegments (sequence, KV head)

@@ -109,7 +109,12 @@ __host__ __device__ __forceinline__ StreamPlan stream_plan_of(long long total, i
 // waves only lengthen the memory's queues (64 sequences, 8 KV heads, D 128,
 // prompts of 1,024-8,192 tokens and 512 generated: 208.8 us with all 2,048,
 // 203.5 with 1,024, 194.7 with 512, 209.8 with 768 and 242 with 384, which
-// leave compute units unevenly loaded; prompts of 4,000: 175.9 -> 160.3).
+// leave compute units unevenly loaded; prompts of 4,000: 175.9 -> 160.3; 8
+// query heads per KV head, 96 of 16,384-32,000: 1,476 -> 1,443, 24 of
+// 8,192-16,384: 204.0 -> 192.6; one query head, 24 of 16,384-32,000: 382.5 ->
+// 367.8; at D 64, with 1,024 for all, 64 of 1,024-8,192: 108.6 -> 104.3, 128 of
+// 4,096-16,384: 419.0 -> 413.2; as one of the distortion's two caches, 24 of
+// 2,048-8,192 in both, 8 query heads per KV head: 191.2 -> 181.1 for the call).
 // LOW pages are bound by the latency of their arithmetic and want every wave
 // (61% LOW: 231 us with 512, 172 with all; 15%: 205.8 and 210.6; 19%: even),
 // and so do calls of many short segments, a few of which each worker would

@@ -1,6 +1,6 @@
 // The work split of attention calls with few segments (pask_plan.h), checked
 // on the CPU over random calls of up to 64 sequences and 128 segments (empty
-// sequences, LOW and window pages, the step's own entry, one or eight KV
+// sequences, LOW and window pages, the step's own entry, one to eight KV
 // heads, head_dim 64 and 128, the workspace's piece bound for any hint): the
 // workers of the launch walk their pieces as the attention kernel does, every
 // page is attended once, no segment has more pieces than the workspace holds,

@@ -57,7 +57,7 @@ def test_controller_bulk_step_and_fused(Hq, Hkv, D):
     """3 sequences, 4 layers in 2 groups, 3 sinks; prompts of 0 / 37 / 300
     tokens kept HIGH (they bypass the controller), then 600 generated tokens
     with tagger tags and parser states: 0..519 bulk-appended in two calls
-    (the controller walks several 256-token chunks), 520..539 one-token
+    (the controller walks several 64-token runs), 520..539 one-token
     appends, 540..599 fused append + attention.  R_0 from beta = 0.33 and
     T_max = 600 runs out part-way, so tokens are both demoted and promoted and
     R ends below zero.  Sequence 2 carries an unknown parser state at two

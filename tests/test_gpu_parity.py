@@ -114,11 +114,11 @@ def test_geometries_mixed_policy(Hq, Hkv, D):
 
 
 @pytest.mark.parametrize("B", [256, 260])
-def test_decode_batch_around_single_call_limit(B):
-    """Up to 256 sequences a decode call with new tokens persists them in its
-    own attention and merge kernels; above, it runs the one-token append
-    kernel first.  Both sides of the limit: ragged short prompts (some empty),
-    mixed HIGH / LOW / DROP tokens, three steps, every sequence compared."""
+def test_decode_batch_around_a_chunk_per_wave(B):
+    """A decode call with new tokens plans 64 sequences per wave of a workgroup
+    at a time: 256 are one chunk for each of the four waves, 260 give the first
+    wave a second, ragged one.  Short prompts (some empty), mixed HIGH / LOW /
+    DROP tokens, three steps, every sequence compared."""
     say(f"case: decode batch {B}")
     pol = make_policy(6, 2, 2, 0.33, seed=900 + B)
     P = [(7 * b) % 45 for b in range(B)]
@@ -266,7 +266,7 @@ def test_flags_bad_tag_capacity_and_pool_exhaustion():
 
 
 def test_call_persisting_its_tokens_flags_and_page_order():
-    """A decode call that persists each sequence's token itself (at most 64
+    """A decode call that persists each sequence's token itself (at most 1,024
     sequences, no window, no parser states): the pages one call opens are
     granted in sequence order, so the first opener takes the last page of a
     pool and the later ones are lost and flagged; a tag outside the table is

@@ -36,8 +36,8 @@ def _windowed(pol, W):
 def test_window_bulk_step_and_fused(Hq, Hkv, D, W):
     """3 sequences, 4 layers in 2 groups, 3 sinks, prompts of 0 / 37 / 300
     tokens kept HIGH (they pass through the window too), then 900 generated
-    tagger-tagged tokens: bulk appends of 5, 195 and 600 tokens (several
-    256-entry chunks, entries leaving from the window and from the call
+    tagger-tagged tokens: bulk appends of 5, 195 and 600 tokens (up to
+    ten 64-token rounds, entries leaving from the window and from the call
     itself), one-token appends, then fused append + attention steps."""
     say(f"case: window W={W} Hq={Hq} Hkv={Hkv} D={D}")
     T = 900
